@@ -72,19 +72,16 @@ typedef struct {
  * verts   device float32 [n_verts][3]
  * tris    device int32   [n_tris][3], vertex indices
  * Builds a bounding-volume hierarchy on the device (Morton-ordered linear BVH,
- * leaves of <= 4 triangles, depth-first node order with skip links), and a
- * copy of its nodes whose boxes are quantised outward to 16 bits per
- * coordinate against the scene's bounding box (16 bytes per node; a box grows
- * by at most 1/65535 of the scene's extent per side, which costs box tests,
- * never a wrong answer), and a 4-wide hierarchy: the binary tree collapsed
- * every other level, each wide node holding the quantised boxes and
- * references of up to four children in one 64-byte segment (one memory round
- * trip tests four boxes).  The build also measures the scene's depth
- * complexity (the leaf boxes' surface areas summed, over the root box's):
- * shadow rays walk the 4-wide hierarchy when it is at least 4 (volume-
- * filling geometry: long walks bound by memory latency), else the binary
- * one (surfaces: short cache-resident walks bound by instruction issue).
- * Either walk gives the same answers.
+ * leaves of at most 2 triangles, depth-first node order with skip links), and a
+ * copy of its nodes whose boxes are quantised outward to half precision
+ * relative to the scene's bounding box (16 bytes per node; a box grows by at
+ * most 1/4096 of the scene's extent per side, which costs box tests, never a
+ * wrong answer), and a 4-wide hierarchy: the binary tree collapsed every other
+ * level, each wide node holding the quantised boxes and references of up to
+ * four children in one 64-byte segment (one memory round trip tests four
+ * boxes).  Shadow rays walk the 4-wide hierarchy; every walk gives the same
+ * answers.  The build also measures the scene's depth complexity (the leaf
+ * boxes' surface areas summed, over the root box's).
  * Big triangles (a box whose longest side is at least 1/8 of the longest side
  * of the triangle centroids' bounds: the walls around a scene, say) form the
  * root's first subtree, one triangle per leaf, when the mesh also has smaller
@@ -116,7 +113,7 @@ typedef struct {
     int32_t max_depth;    /* longest root-to-leaf path */
     int32_t bad_tris;     /* triangles replaced by degenerate ones */
     int32_t n_groups;     /* 4-wide nodes */
-    int32_t wide;         /* 1: shadow rays walk the 4-wide hierarchy, 0: the binary one */
+    int32_t wide;         /* 1: volume-filling geometry (depth complexity of at least 4), 0: surfaces */
     float depth_complexity; /* sum of the leaf boxes' surface areas over the root box's */
     int32_t n_big;        /* big triangles (see mcdi_build_scene) */
 } mcdi_scene_info_t;

@@ -5,7 +5,7 @@
 // puts the mesh's big triangles first, see morton()), a radix sort, the
 // binary radix tree of the sorted codes built in parallel (one lane per
 // internal node, Karras 2012), box fitting and the counts of the nodes that
-// survive collapsing subtrees of <= 4 triangles (1 among the big ones) into
+// survive collapsing subtrees of <= kLeafMax triangles (1 among the big ones) into
 // leaves, and a final pass that writes every surviving node at its depth-first
 // pre-order index with a skip link, so traversal needs no stack.
 //
@@ -422,48 +422,57 @@ __global__ __launch_bounds__(256) void fit_top(int nt, Tree T) {
     T.cnt[p] = 2 * (leaves_before(T, nt, l + 1) - leaves_before(T, nt, f)) - 1;
 }
 
-// Quantisation frame of the scene from its root box: base below the box and
-// a step such that base + 65535 step lies above it, both with a pad of
-// 2^-20 of the largest extent, base rounded down and step up to FP32.
+// Quantisation frame of the scene from its root box: the box's middle rounded
+// to FP32, and a step such that mid -/+ 2^15 step lie outside the box with a
+// pad of 2^-20 of the largest extent, rounded up to FP32.
 __device__ void qframe_of(float4 rlo, float4 rhi, QFrame& F) {
     const double ext = fmax(fmax((double)rhi.x - rlo.x, (double)rhi.y - rlo.y), (double)rhi.z - rlo.z);
     const double pad = fmax(ext * 0x1p-20, 1e-30);
     const double lo[3] = {rlo.x, rlo.y, rlo.z}, hi[3] = {rhi.x, rhi.y, rhi.z};
     for (int a = 0; a < 3; ++a) {
-        F.base[a] = __double2float_rd(lo[a] - pad);
-        F.step[a] = __double2float_ru((hi[a] + pad - (double)F.base[a]) / 65535.0);
+        F.mid[a] = (float)(0.5 * (lo[a] + hi[a]));
+        const double reach = fmax(hi[a] - (double)F.mid[a], (double)F.mid[a] - lo[a]) + pad;
+        F.step[a] = __double2float_ru(reach * 0x1p-15);
     }
 }
 
-// Outward 16-bit quantisation: the plane of q_lo is at or below lo, that of
-// q_hi at or above hi (exact in FP64: q * step needs at most 41 bits).  A
-// non-finite coordinate gives the whole range.
-__device__ uint32_t quant_lo(float v, float base, float step) {
-    if (!isfinite(v)) return 0u;
-    double q = floor(((double)v - base) / step);
-    q = fmin(fmax(q, 0.0), 65535.0);
-    while (q > 0.0 && (double)base + q * (double)step > (double)v) q -= 1.0;
-    return (uint32_t)q;
+// Bits of the largest half <= x (|x| <= 2^15): x in units of its half's last
+// place, rounded down (subnormals below 2^-14 have a last place of 2^-24).
+__device__ uint32_t half_down(double x) {
+    if (x == 0.0) return 0u;
+    int e = 0;
+    (void)frexp(fabs(x), &e);
+    const int k = max(e - 11, -24);
+    const double v = ldexp(floor(ldexp(x, -k)), k);
+    return __builtin_bit_cast(uint16_t, (_Float16)(float)v);
 }
-__device__ uint32_t quant_hi(float v, float base, float step) {
-    if (!isfinite(v)) return 65535u;
-    double q = ceil(((double)v - base) / step);
-    q = fmin(fmax(q, 0.0), 65535.0);
-    while (q < 65535.0 && (double)base + q * (double)step < (double)v) q += 1.0;
-    return (uint32_t)q;
+__device__ double half_value(uint32_t h) { return (double)(float)__builtin_bit_cast(_Float16, (uint16_t)h); }
+
+// Outward quantisation: the plane of lo is at or below v.  A non-finite
+// coordinate gives the end of the range.  (The plane is formed in FP64 and
+// stepped down while the division's rounding left it above v.)
+__device__ uint32_t quant_lo(float v, double mid, float step) {
+    constexpr uint32_t kEnd = 0xF800u;   // -2^15
+    if (!isfinite(v)) return kEnd;
+    uint32_t h = half_down(fmin(fmax(((double)v - mid) / step, -0x1p15), 0x1p15));
+    for (int k = 0; k < 4 && h != kEnd && mid + half_value(h) * (double)step > (double)v; ++k)
+        h = (h & 0x7FFFu) == 0u ? 0x8001u : ((h & 0x8000u) ? h + 1u : h - 1u);
+    return h;
 }
+// the plane of hi is at or above v
+__device__ uint32_t quant_hi(float v, double mid, float step) { return quant_lo(-v, -mid, step) ^ 0x8000u; }
 
 __device__ QNode quantise(const QFrame& F, const Node& nd) {
     uint32_t l[3], h[3];
     for (int a = 0; a < 3; ++a) {
-        l[a] = quant_lo(nd.lo[a], F.base[a], F.step[a]);
-        h[a] = quant_hi(nd.hi[a], F.base[a], F.step[a]);
+        l[a] = quant_lo(nd.lo[a], F.mid[a], F.step[a]);
+        h[a] = quant_hi(nd.hi[a], F.mid[a], F.step[a]);
     }
     QNode q;
     q.x = l[0] | (l[1] << 16);
     q.y = l[2] | (h[0] << 16);
     q.z = h[1] | (h[2] << 16);
-    q.w = nd.payload != 0 ? (kQLeaf | (uint32_t)nd.payload) : (uint32_t)nd.escape;
+    q.w = nd.payload != 0 ? leaf_ref((uint32_t)nd.payload >> 3, (uint32_t)nd.payload & 7u) : (uint32_t)nd.escape;
     return q;
 }
 
@@ -513,13 +522,22 @@ __global__ __launch_bounds__(256) void emit(int nt, Tree T, Node* out, QNode* qo
     if (x == 0) info->n_nodes = T.cnt[0];
 }
 
+// rows (v0, v1, v2, 0) of x, y and z from vertices, or vertices from rows
+__device__ __forceinline__ void transpose_tri(const float4* t, float4* out) {
+    const float4 a = t[0], b = t[1], c = t[2];
+    out[0] = make_float4(a.x, b.x, c.x, 0.0f);
+    out[1] = make_float4(a.y, b.y, c.y, 0.0f);
+    out[2] = make_float4(a.z, b.z, c.z, 0.0f);
+}
+
 __global__ void reorder(const float4* tmp, const uint32_t* vals, int64_t nt, float4* out) {
     const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= nt) return;
-    const float4* t = tmp + 3 * (size_t)vals[k];
-    out[3 * k] = t[0];
-    out[3 * k + 1] = t[1];
-    out[3 * k + 2] = t[2];
+    if (k < nt) transpose_tri(tmp + 3 * (size_t)vals[k], out + 3 * k);
+}
+
+__global__ __launch_bounds__(256) void tri_vertices(const float4* rows, int64_t n, float4* verts) {
+    const int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (k < n) transpose_tri(rows + 3 * k, verts + 3 * k);
 }
 
 // The 4-wide hierarchy of the shadow-ray traversal, collapsed from the binary
@@ -528,33 +546,22 @@ __global__ void reorder(const float4* tmp, const uint32_t* vals, int64_t nt, flo
 // replaced by its own two children.  Slots 0-1 hold what N's first child
 // contributes (itself when it is a leaf, else its two children), slots 2-3
 // what the second contributes; a child record is the quantised box of that
-// binary node with w = its wide node's index (internal) or kQLeaf | payload
-// (leaf), and an unused slot holds an empty record (lo > hi: no ray hits it);
-// every record's w also carries kRefLive.
+// binary node with w = its wide node's index (internal) or its leaf reference,
+// and an unused slot holds an empty record (lo > hi: no ray hits it).
 // Wide nodes are numbered in the binary pre-order of their nodes (an
 // exclusive scan of the flags), so the wide hierarchy is in pre-order too.
 //
-// Beside each wide node, its visit order: for each of the eight octants of a
-// ray direction (bit a set where the component on axis a is negative), three
-// bits -- swap slots 0 and 1, swap slots 2 and 3, swap the two pairs -- that
-// put each binary split's child farther along the ray after the nearer one in
-// slot order (the big triangles' child after the other at the split that
-// separates them).  The walk pushes hit children in slot order and pops the
-// last pushed, so it descends into the farther child first.
+// The records' words also carry the axes of the up to three binary splits a
+// wide node covers.  A ray takes each split's child farther along the ray on
+// the split's axis first (the Morton order puts the lower side left), and at
+// the split that separates the big triangles (axis 3) their child first.
 __device__ __forceinline__ QNode empty_record() {
     QNode q;
-    q.x = 0xFFFFFFFFu;   // lo.x = lo.y = 65535
-    q.y = 0x0000FFFFu;   // lo.z = 65535, hi.x = 0
-    q.z = 0u;            // hi.y = hi.z = 0
-    q.w = kQLeaf;        // an empty leaf, should it ever be taken
+    q.x = 0x7BFF7BFFu;   // lo = 65504, the largest half, hi = -65504
+    q.y = 0xFBFF7BFFu;
+    q.z = 0xFBFFFBFFu;
+    q.w = kEmptyRef;     // tests nothing, should it ever be taken
     return q;
-}
-
-// 1 when a ray of octant o should take the split's left child first: the
-// left child lies farther along the ray on the split's axis, or holds the big
-// triangles (axis 3)
-__device__ __forceinline__ uint32_t left_first(int axis, int o) {
-    return axis == 3 ? 1u : (uint32_t)((o >> axis) & 1);
 }
 
 __device__ __forceinline__ QNode child_record(const Node* out, const QNode* qout, const int32_t* gidx, int x) {
@@ -565,41 +572,33 @@ __device__ __forceinline__ QNode child_record(const Node* out, const QNode* qout
 
 __global__ __launch_bounds__(256) void wide_groups(const Node* out, const QNode* qout, const int32_t* gflag,
                                                    const int32_t* gidx, const int32_t* naxis, int n_max,
-                                                   QNode* groups, uint32_t* gorder, DeviceSceneInfo* info) {
+                                                   QNode* groups, DeviceSceneInfo* info) {
     const int x = blockIdx.x * blockDim.x + threadIdx.x;
     if (x >= n_max) return;
     const int n_nodes = out[0].escape;            // surviving binary nodes
     if (x >= n_nodes || !gflag[x]) return;
     const int self = gidx[x];
-    QNode* g = groups + 4 * (size_t)self;
+    QNode g[4];
     for (int k = 0; k < 4; ++k) g[k] = empty_record();
-    uint32_t order = 0u;
+    uint32_t axis[3] = {0u, 0u, 0u};
     if (out[x].payload != 0) {                    // a root that is a leaf
         g[0] = child_record(out, qout, gidx, x);
     } else {
         const int c[2] = {x + 1, out[x + 1].escape};
-        int sub_axis[2] = {-1, -1};
+        axis[0] = (uint32_t)naxis[x];
         for (int i = 0; i < 2; ++i) {
             const int y = c[i];
             if (y <= x || y >= n_nodes) continue;    // never for a valid tree
             if (out[y].payload != 0) {
                 g[2 * i] = child_record(out, qout, gidx, y);
             } else {
-                sub_axis[i] = naxis[y];
+                axis[1 + i] = (uint32_t)naxis[y];
                 const int d[2] = {y + 1, out[y + 1].escape};
                 for (int j = 0; j < 2; ++j)
                     if (d[j] > y && d[j] < n_nodes) g[2 * i + j] = child_record(out, qout, gidx, d[j]);
             }
         }
-        const int top = naxis[x];
-        for (int o = 0; o < 8; ++o) {
-            uint32_t f = left_first(top, o) << 2;
-            if (sub_axis[0] >= 0) f |= left_first(sub_axis[0], o);
-            if (sub_axis[1] >= 0) f |= left_first(sub_axis[1], o) << 1;
-            order |= f << (3 * o);
-        }
     }
-    gorder[self] = order;
     // the walk's termination rests on this: every internal child reference
     // lies past its parent and inside the node array (pre-order numbering);
     // a violation (never for a valid tree) sends the scene to the binary walk
@@ -607,12 +606,63 @@ __global__ __launch_bounds__(256) void wide_groups(const Node* out, const QNode*
     for (int i = 0; i < 4; ++i) {
         const uint32_t w = g[i].w;
         if (!(w & kQLeaf) && ((int)w <= self || (int)w >= n_groups)) atomicOr(&info->wide_bad, 1);
-        g[i].w = w | kRefLive;
+        g[i].w = (w & kRefMask) | kRefLive | (i < 3 ? axis[i] << kRefAxisShift : 0u);
+        groups[4 * (size_t)self + i] = g[i];
+    }
+}
+
+// Hoisted nodes (one wavefront): breadth-first from the root, one level a
+// step with a lane to each of its nodes, until kTopNodes are taken.  Only as
+// many levels as a full 4-ary tree needs twice over: what a thinner tree
+// leaves out stays in the node array.
+constexpr int kTopLevels = 6;
+__global__ __launch_bounds__(64) void hoist_top(const QNode* groups, QNode* top) {
+    static_assert(kTopNodes <= 64, "a lane to each node of a level");
+    __shared__ uint32_t s_list[kTopNodes];
+    const int t = threadIdx.x;
+    int begin = 0, end = 1;
+    if (t == 0) s_list[0] = 0u;
+    __syncthreads();
+    for (int level = 0; begin < end; ++level) {
+        const bool mine = begin + t < end;
+        QNode g[4];
+        int n = 0;
+        if (mine) {
+            const QNode* src = groups + 4 * (size_t)s_list[begin + t];
+            for (int k = 0; k < 4; ++k) {
+                g[k] = src[k];
+                n += (g[k].w & kQLeaf) ? 0 : 1;
+            }
+        }
+        // internal children before this lane's on the level
+        int incl = n;
+        for (int o = 1; o < 64; o <<= 1) {
+            const int v = __shfl_up(incl, o);
+            incl += t >= o ? v : 0;
+        }
+        int at = end + incl - n;
+        const int total = __shfl(incl, 63);
+        const int next_end = level + 1 < kTopLevels ? min(end + total, kTopNodes) : end;
+        if (mine) {
+            for (int k = 0; k < 4; ++k) {
+                if (!(g[k].w & kQLeaf)) {
+                    if (at < next_end) {
+                        s_list[at] = g[k].w & (kRefTop - 1u);
+                        g[k].w = (g[k].w & ~(kRefTop - 1u)) | kRefTop | (uint32_t)at;
+                    }
+                    ++at;
+                }
+                top[4 * (begin + t) + k] = g[k];
+            }
+        }
+        begin = end;
+        end = next_end;
+        __syncthreads();
     }
 }
 
 __global__ void tiny_scene(const float4* tmp, int nt, Node* out, float4* tris_out, QNode* qout, QFrame* frame,
-                           DeviceSceneInfo* info, QNode* groups, uint32_t* gorder) {
+                           DeviceSceneInfo* info, QNode* groups, QNode* top) {
     Node nd;
     if (nt == 0) {
         for (int k = 0; k < 3; ++k) { nd.lo[k] = 0.0f; nd.hi[k] = 0.0f; }
@@ -626,7 +676,7 @@ __global__ void tiny_scene(const float4* tmp, int nt, Node* out, float4* tris_ou
         nd.hi[0] = hi.x; nd.hi[1] = hi.y; nd.hi[2] = hi.z;
         nd.escape = 1;
         nd.payload = (0 << 3) | 1;
-        tris_out[0] = tmp[0]; tris_out[1] = tmp[1]; tris_out[2] = tmp[2];
+        transpose_tri(tmp, tris_out);
         info->n_nodes = 1;
     }
     out[0] = nd;
@@ -637,8 +687,10 @@ __global__ void tiny_scene(const float4* tmp, int nt, Node* out, float4* tris_ou
     info->max_depth = 0;
     groups[0] = nt == 0 ? empty_record() : qout[0];
     for (int k = 1; k < 4; ++k) groups[k] = empty_record();
-    for (int k = 0; k < 4; ++k) groups[k].w |= kRefLive;
-    gorder[0] = 0u;
+    for (int k = 0; k < 4; ++k) {
+        groups[k].w |= kRefLive;
+        top[k] = groups[k];
+    }
     info->n_groups = 1;
 }
 
@@ -687,6 +739,11 @@ __global__ void choose_walk(const Node* out, DeviceSceneInfo* info) {
 inline unsigned nblk(int64_t n) { return (unsigned)((n + 255) / 256); }
 
 }  // namespace
+
+hipError_t launch_tri_vertices(const float4* rows, int64_t n, float4* verts, hipStream_t s) {
+    if (n > 0) hipLaunchKernelGGL(tri_vertices, dim3(nblk(n)), dim3(256), 0, s, rows, n, verts);
+    return hipGetLastError();
+}
 
 hipError_t build_bvh(const float* verts, int64_t nv, const int32_t* tris, int64_t nt64, Node* nodes_out,
                      float4* tris_out, QNode* qnodes_out, QFrame* frame_out, QNode* groups_out,
@@ -754,8 +811,8 @@ hipError_t build_bvh(const float* verts, int64_t nv, const int32_t* tris, int64_
     int32_t* gidx = (int32_t*)take(sz_i);
     int32_t* naxis = (int32_t*)take(sz_i);
     void* scan_tmp = take(sz_scan);
-    // the visit orders follow the wide nodes in the same allocation
-    uint32_t* gorder = reinterpret_cast<uint32_t*>(groups_out + 4 * ntm);
+    // the hoisted nodes follow the wide nodes in the same allocation
+    QNode* top = groups_out + 4 * ntm;
     T.nb = nb;
     T.levels = levels;
     T.nbig = &info->n_big;
@@ -766,7 +823,7 @@ hipError_t build_bvh(const float* verts, int64_t nv, const int32_t* tris, int64_
     }
     if (nt <= 1) {
         hipLaunchKernelGGL(tiny_scene, dim3(1), dim3(1), 0, s, tmp, nt, nodes_out, tris_out, qnodes_out, frame_out,
-                           info, groups_out, gorder);
+                           info, groups_out, top);
     } else {
         hipLaunchKernelGGL(morton, dim3(nblk(nt)), dim3(256), 0, s, tmp, (int64_t)nt, cb, keys, vals, info);
         err = rocprim::radix_sort_pairs(sort_tmp, sort_bytes, keys, keys2, vals, vals2, (size_t)nt, 0, 64, s);
@@ -788,7 +845,8 @@ hipError_t build_bvh(const float* verts, int64_t nv, const int32_t* tris, int64_
         }
         if (err == hipSuccess) {
             hipLaunchKernelGGL(wide_groups, dim3(nblk(2 * nt - 1)), dim3(256), 0, s, nodes_out, qnodes_out, gflag,
-                               gidx, naxis, 2 * nt - 1, groups_out, gorder, info);
+                               gidx, naxis, 2 * nt - 1, groups_out, info);
+            hipLaunchKernelGGL(hoist_top, dim3(1), dim3(64), 0, s, groups_out, top);
             hipLaunchKernelGGL(count_groups, dim3(1), dim3(1), 0, s, gflag, gidx, 2 * nt - 1, info);
             hipLaunchKernelGGL(leaf_area_sum, dim3(nblk(2 * nt - 1)), dim3(256), 0, s, nodes_out, 2 * nt - 1, info);
             hipLaunchKernelGGL(choose_walk, dim3(1), dim3(1), 0, s, nodes_out, info);

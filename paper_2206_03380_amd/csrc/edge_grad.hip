@@ -281,8 +281,7 @@ __device__ __forceinline__ bool wave_anyhit(const Scene& sc, const Ray& r, int n
                 const int first = payload >> 3;
                 const int cnt = (first + (payload & 7) <= sc.n_tris) ? (payload & 7) : 0;
                 for (int k = 0; k < cnt && !hit; ++k) {
-                    const float4* t = sc.tris + 3 * (first + k);
-                    hit = tri_anyhit(r, t[0], t[1], t[2]);
+                    hit = tri_anyhit(r, sc.tris + 3 * (size_t)(first + k));
                 }
                 i = next;
             }

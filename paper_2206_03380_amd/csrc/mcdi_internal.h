@@ -19,7 +19,13 @@ struct alignas(16) Node {
     int32_t payload;
 };
 
-constexpr int kLeafMax = 4;
+// Triangles a leaf holds at most.  A gather of a triangle costs the traversal
+// three of the L1 cache's slow gathers, a node in LDS none: leaves of 4, 3, 2
+// and 1 take the shadow rays of a 102k-triangle surface (1.05M pixels at 12
+// spp) 1.83, 1.75, 1.70 and 1.70 ms, of a room of 1.0M triangles (4.2M pixels
+// at 32 spp) 5.6, 5.7, 5.4 and 5.4 ms; single triangles need half as many
+// nodes again and build 1% slower.
+constexpr int kLeafMax = 2;
 // Big triangles: a triangle whose box's longest side is at least 1/kBigTriDiv
 // of the longest side of the triangle centroids' bounds.  When a mesh has both
 // big and small ones, the big ones form the root's first subtree, in leaves of
@@ -34,61 +40,85 @@ struct DeviceSceneInfo {
     int32_t max_depth;
     int32_t bad_tris;
     int32_t n_groups;          // wide nodes
-    int32_t wide;              // 1: shadow rays walk the wide hierarchy
+    int32_t wide;              // 1: volume-filling (depth complexity of at least kWideDepthComplexity)
     float depth_complexity;    // sum of leaf box areas / root box area
     int32_t wide_bad;          // a wide reference failed the builder's check
     int32_t n_big;             // big triangles (the root's first subtree when 0 < n_big < n_tris)
     double leaf_area;          // the sum (accumulated by the builder)
 };
 
-// The scene's quantisation frame: node box coordinates as 16-bit integers q,
-// the plane q standing for base + q * step (per axis).
+// The scene's quantisation frame: node box coordinates as half-precision
+// values v in [-2^15, 2^15], the plane v standing for mid + v * step (per axis;
+// the scene's box spans that range).  A half holds 11 bits, so a box grows by
+// at most 2^-12 of the scene's extent per side far from the middle and by less
+// towards it.
 struct QFrame {
-    float base[3];
+    float mid[3];
     float step[3];
 };
 
 // Compact node of the shadow-ray traversal (16 bytes, one load): the box of
 // the Node with the same index quantised against the frame outward (lo
 // rounded down, hi rounded up: it contains the exact box) and one link word.
-//   x = qlo.x | qlo.y << 16, y = qlo.z | qhi.x << 16, z = qhi.y | qhi.z << 16
-//   w = leaf: 0x80000000 | payload (first_triangle << 3 | count), its
-//       escape being the next index; internal: the escape index
+//   x = lo.x | lo.y << 16, y = lo.z | hi.x << 16, z = hi.y | hi.z << 16
+//       (the bits of the halves)
+//   w = leaf: a leaf reference, its escape being the next index; internal: the
+//       escape index
 struct QNode {
     uint32_t x, y, z, w;
 };
+
+// Leaf reference: kQLeaf | first triangle << 2 | count - 1 (count 1..4, first
+// triangle below 2^26).
 constexpr uint32_t kQLeaf = 0x80000000u;
-// Set in every child reference of a wide node (references stay below 2^29):
-// a walk replaces the reference of a child whose box it missed by 0 and
-// pushes the rest, advancing its stack past each reference that has the bit.
-constexpr uint32_t kRefLive = 1u << 30;
+__host__ __device__ constexpr uint32_t leaf_ref(uint32_t first, uint32_t count) {
+    return kQLeaf | (first << 2) | (count - 1u);
+}
+// the reference of an empty record: past every triangle array
+constexpr uint32_t kEmptyRef = leaf_ref((1u << 26) - 1u, 1u);
 
 // Wide node of the shadow-ray traversal: four child records in QNode form
 // (64 bytes, one aligned segment), w = the child's wide-node index (internal)
-// or kQLeaf | payload (leaf); unused slots have an empty box.  Node 0 is the
-// root.
-constexpr uint32_t kWideNone = 0xFFFFFFFFu;   // no node (a traversal state)
+// or a leaf reference; unused slots have an empty box.  Node 0 is the root.
+// A child's word also carries
+//   kRefLive  always: a walk replaces the reference of a child whose box it
+//             missed by 0 and pushes the rest, advancing its stack past each
+//             reference that has the bit;
+//   kRefTop   the index is one of the hoisted nodes (below);
+//   bits 28-29 of slots 0, 1 and 2: the axis of the node's own binary split
+//             (3: the split that separates the big triangles), of its first
+//             and of its second child's, from which the walk derives the
+//             order it takes the children in (no separate load: the L1 cache
+//             spends as long on a gather of 4 bytes a lane as on one of 16).
+constexpr uint32_t kRefLive = 1u << 30;
+constexpr uint32_t kRefTop = 1u << 27;
+constexpr uint32_t kRefMask = kQLeaf | 0x0FFFFFFFu;   // the reference itself
+constexpr int kRefAxisShift = 28;
+constexpr uint32_t kWideNone = kRefMask;   // no node (a traversal state; never a leaf reference, see kEmptyRef)
+
+// Hoisted nodes: copies of the first wide nodes in breadth-first order from
+// the root, whose references to one another are their numbers in that order
+// with kRefTop.  Workgroups of the traversal hold them in LDS.
+constexpr int kTopNodes = 30;
 
 struct Scene {
     const Node* nodes;    // [>= 1]
-    const float4* tris;   // [3 * n_tris] vertex positions, w unused
+    const float4* tris;   // [3 * n_tris] rows (v0, v1, v2, 0) of each triangle's x, y and z, in leaf order
     int64_t n_tris;
     const QNode* qnodes;  // [>= 1] the same nodes, quantised
     const QFrame* frame;
     const QNode* groups;  // [4 * capacity] wide nodes
     uint32_t group_bytes; // 64 * capacity (the bound of a buffer resource)
-    const uint32_t* gorder;   // [capacity] each wide node's visit orders (per ray octant)
-    const DeviceSceneInfo* info;   // info->wide selects the traversal (read by the kernels)
+    const QNode* top;     // [4 * kTopNodes] hoisted wide nodes
+    const DeviceSceneInfo* info;
 };
 
-// Traversal choice, made by the builder on the device.  The depth
-// complexity -- the surface areas of the leaf boxes summed, over the root
-// box's -- estimates how many leaves a ray through the scene crosses.  Surface
-// scenes (about 1.5 for the displaced spheres) are walked on the binary
-// hierarchy, whose cache-resident walk is bound by instruction issue;
-// volume-filling ones (16 for the beam lattice in its room, 95 for the beams
-// alone), whose rays cross many boxes and whose walk is bound by memory round
-// trips, on the 4-wide hierarchy (about a quarter of the round trips).
+// Depth complexity: the surface areas of the leaf boxes summed, over the root
+// box's, which estimates how many leaves a ray through the scene crosses:
+// under 2 for surfaces such as the displaced spheres, 18 for the beam lattice
+// in its room.  From this value on a scene counts as volume-filling
+// (DeviceSceneInfo::wide), where the one-lane walk of the edge gradient's
+// out-side rays takes the 4-wide hierarchy.
 constexpr float kWideDepthComplexity = 4.0f;
 
 struct EnvView {
@@ -204,6 +234,8 @@ hipError_t launch_shade_bwd(const ShadeArgs& a, hipStream_t s);
 // visibility from a.g, the material and the probe radiance evaluated from
 // a.e_* and a.env.tex (whose w, the density, is the sampling probe's)
 hipError_t launch_shade_fwd_frozen(const ShadeArgs& a, hipStream_t s);
+// vertices (x, y, z, 0) of n triangles from their rows
+hipError_t launch_tri_vertices(const float4* rows, int64_t n, float4* verts, hipStream_t s);
 hipError_t launch_trace(const Scene& sc, const float* o, const float* d, int64_t n, uint8_t* hit,
                         int brute, hipStream_t s);
 
@@ -275,7 +307,7 @@ struct TempAlloc {
     void* ctx;
 };
 // groups_out: capacity for max(1, n_tris) wide nodes (>= internal nodes + 1),
-// followed by as many 32-bit visit orders
+// followed by the kTopNodes hoisted ones
 hipError_t build_bvh(const float* verts, int64_t n_verts, const int32_t* tris, int64_t n_tris,
                      Node* nodes_out, float4* tris_out, QNode* qnodes_out, QFrame* frame_out, QNode* groups_out,
                      DeviceSceneInfo* info, const TempAlloc& ta, hipStream_t s, int* oom);

@@ -427,374 +427,230 @@ __device__ __forceinline__ void gen_tile(const ShadeArgs& A, int64_t tile, float
     }
 }
 
-// 2) any-hit traversal of the tile's ray region.  Lanes that finish a ray
-//    take the next one from the region (one LDS atomic per wave per refill);
-//    box steps and triangle steps run in separate phases so a wave keeps its
-//    lanes on the same code (while-while traversal with dynamic fetch).
+// 2) any-hit traversal of the tile's ray region over the 4-wide hierarchy.
+//    Lanes that finish a ray take the next one from the region (one LDS atomic
+//    per wave per refill); box steps and triangle steps run in separate phases
+//    so a wave keeps its lanes on the same code (while-while traversal with
+//    dynamic fetch).
 //
-//    Per lane: the next node to test (n_total once the walk is over, or when
-//    the lane holds no ray) and up to two postponed leaves, kept as their
-//    packed payload words (first_triangle << 3 | count; 0 = none).  Testing
-//    one triangle of a leaf advances its word by 7: the first index grows by
-//    one and the count drops by one.  The second slot is only used while the
-//    first is pending.
-// Binary walk: pre-order with skip links, one 16-byte node per step, no stack.
+//    Per lane: the next node (a wide node to visit; a leaf reference that
+//    waits for the pending slot; kWideNone, the walk is over or the lane holds
+//    no ray) and one postponed leaf (its reference, 0 = none).  Testing one
+//    triangle of a leaf with more advances its reference by 3: the first
+//    index grows by one and the rest drops by one.
+//
+//    What bounds it: instruction issue (99% of the vector issue slots on a
+//    room of 1.0M triangles) and, where the nodes come from the L1 cache, its
+//    gathers: 64 lanes at 64 addresses take it about 45 cycles whether a lane
+//    fetches 4 bytes or 16 and whether the four loads of a node share a line
+//    (measured), so a wide node costs 180 of them beside 110 cycles of its
+//    CU's vector issue.  The root's first kTopNodes descendants are therefore
+//    read from LDS (81% of the visits in the room, 30% on a surface), the
+//    visit order comes with the records instead of by a fifth load, and the
+//    loop holds one walk: a ray whose stack overflows, and it alone, walks the
+//    binary nodes after the visits of the step.
+//    Shadow rays, before (two walks in the loop, a separate order word, two
+//    pending leaves, no hoisted nodes) -> after: 4.2M pixels at 32 spp in the
+//    room 10.6 -> 7.1 ms, 1.05M pixels at
+//    12 spp on a 102k-triangle surface 2.36 -> 1.70 ms, 201k pixels at 16 spp
+//    on a 45k-triangle one 545 -> 385 us, 4096 pixels at 4 spp 45 -> 30 us.
+//
+// Pending references of the wide traversal, per lane, in LDS: row k of the
+// workgroup's lane t at [k * kBlock + t] (lanes of a wave hit distinct banks
+// whatever their stack depths).  Row 0 holds kWideNone, so that popping an
+// empty stack ends the walk without a test.  Up to kStack + 1 references
+// after a visit's pushes (the visit pops one again), and three spare rows for
+// its last stores.  Eight workgroups per CU fit, with the hoisted nodes.
+constexpr int kStack = 13, kStackRows = 1 + kStack + 4;
+
 template <bool COUNT>
-__device__ __forceinline__ void trace_tile_binary(const ShadeArgs& A, int64_t tile, const float4* R, int count,
-                                                  uint32_t* hitbits, int* s_next) {
+__device__ __forceinline__ void trace_tile(const ShadeArgs& A, int64_t tile, const float4* R, int count,
+                                           uint32_t* hitbits, int* s_next, uint32_t* s_stack, uint4* s_top) {
     const Scene& sc = A.scene;
     const int64_t N = A.g.n;
     const int64_t base_pix = tile * kBlock;
     const int n_total = sc.nodes[0].escape;
     const uint32_t n_tris = (uint32_t)sc.n_tris;
     const QFrame F = *sc.frame;
+    // a hierarchy that failed the builder's check (never for a valid tree):
+    // every ray walks the binary nodes
+    const bool flat = sc.info->wide_bad != 0;
     const char* tri_bytes = reinterpret_cast<const char*>(sc.tris);
-    const __amdgpu_buffer_rsrc_t qrs = __builtin_amdgcn_make_buffer_rsrc(
-        (void*)sc.qnodes, (short)0, (int)((uint32_t)n_total * 16u), kBufferWord3);
+    // nodes as a buffer resource: 32-bit offsets, and a load past the end
+    // returns zeros instead of reading out of bounds
+    const __amdgpu_buffer_rsrc_t grs = __builtin_amdgcn_make_buffer_rsrc(
+        (void*)sc.groups, (short)0, (int)sc.group_bytes, kBufferWord3);
+    for (int k = threadIdx.x; k < 4 * kTopNodes; k += kBlock) s_top[k] = reinterpret_cast<const uint4*>(sc.top)[k];
+    s_stack[threadIdx.x] = kWideNone;
+    __syncthreads();
+    // the stack's first free row as a byte offset
+    constexpr uint32_t kRow = 4u * kBlock, kOverflow = (1u + kStack + 1u) * kRow;
+    const uint32_t sp0 = 4u * threadIdx.x + kRow, sp_end = 4u * threadIdx.x + kOverflow;
+    uint32_t sp = sp0;
+    auto row = [&](uint32_t at) -> uint32_t& {
+        return *reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(s_stack) + at);
+    };
     const int lane = __lane_id();
     const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-    bool active = false, exhausted = false;
+    bool exhausted = n_total <= 0;   // uniform: no ray is left to take
     Ray ray;
     QRay qray;
-    int node = n_total;
-    uint32_t p0 = 0u, p1 = 0u;
+    uint32_t oct = 0u;     // the ray's octant
+    // (every wide walk ends: the builder checked that each internal child
+    // reference is larger than its parent's index and smaller than the node
+    // count)
+    uint32_t node = kWideNone, p0 = 0u;
     uint32_t tag = 0u;     // the ray's pixel within the tile | sample slot << 8
+    bool restart = false;  // the stack overflowed
     uint32_t c_hits = 0, c_box = 0, c_tri = 0, c_bstep = 0, c_tstep = 0;   // steps: lane 0 only
     uint32_t c_blane = 0;
-    // scheduling knobs: refill batch, node steps per phase check, and the
-    // phase hand-over ratios (in halves)
-    constexpr int kRefillMin = 32, kBoxSteps = 2, kBoxSwitch2 = 2, kTriSwitch2 = 2;
+    auto report = [&]() {
+        const uint32_t slot = tag >> 8;
+        atomicOr(hitbits + (int64_t)(slot >> 5) * N + base_pix + (tag & 255u), 1u << (slot & 31));
+        if (COUNT) ++c_hits;
+    };
+    // scheduling knobs: refill batch, node visits per phase check, and the
+    // phase hand-over ratios (the box phase ends once four times the lanes
+    // stuck on leaves are as many as the walkers, the triangle phase once the
+    // lanes free to walk are more than twice the testers).  Measured on the
+    // room below: 3, 4, 5, 6 and 7 visits 6.3, 5.3, 5.4, 5.8 and 6.3 ms; the
+    // other knobs a step up or down stay within 3%.
+    constexpr int kRefillMin = 16, kBoxSteps = 4, kBoxSwitch4 = 1, kTriSwitch2 = 4;
     while (true) {
-        // refill when half of the wave is idle, or when nobody is busy
-        const uint64_t need = __ballot(!active && !exhausted);
-        const uint64_t busy = __ballot(active);
-        if (need && (__popcll(need) >= kRefillMin || busy == 0ull)) {
-            const int leader = __ffsll((unsigned long long)need) - 1;
-            int b = 0;
-            if (lane == leader) b = atomicAdd(s_next, (int)__popcll(need));
-            b = __shfl(b, leader);
-            if (!active && !exhausted) {
+        // refill when a quarter of the wave is idle, or when nobody is busy
+        if (!exhausted) {
+            const bool idle = node == kWideNone && p0 == 0u;
+            const uint64_t need = __ballot(idle);
+            const int n_need = (int)__popcll(need);
+            if (n_need >= kRefillMin) {
+                int b = 0;
+                if (lane == 0) b = atomicAdd(s_next, n_need);
+                b = __builtin_amdgcn_readfirstlane(b);
+                exhausted = b + n_need >= count;
                 const int idx = b + (int)__popcll(need & lt);
-                if (idx < count) {
+                if (idle && idx < count) {
                     const float4 rr = R[idx];
                     tag = __float_as_uint(rr.w);
                     const float4 o = A.origins[base_pix + (tag & 255u)];
                     ray = make_ray(f3(o.x, o.y, o.z), f3(rr.x, rr.y, rr.z));
                     qray = make_qray(ray, F);
-                    node = 0;
-                    p0 = p1 = 0u;
-                    active = n_total > 0;
-                } else {
-                    exhausted = true;
+                    oct = ray_octant(f3(rr.x, rr.y, rr.z));
+                    node = flat ? kWideNone : kRefTop;   // the root, hoisted node 0
+                    restart = flat;
+                    sp = sp0;
                 }
             }
         }
-        if (!__any(active)) {
-            if (!__any(!exhausted)) break;
-            continue;
-        }
-        // box phase: a lane walks while its second leaf slot is free and the
-        // tree is not finished (a leaf found with the first slot taken goes
-        // to the second); the phase ends once the lanes that hold a leaf and
-        // cannot walk are at least as many as the lanes still walking
+        // box phase: lanes visit wide nodes; a lane whose next node is a leaf
+        // waits for its pending slot
         while (true) {
-            if (!__any(node < n_total && p1 == 0u)) break;
 #pragma unroll
             for (int step = 0; step < kBoxSteps; ++step) {
-                const bool walking = node < n_total && p1 == 0u;
+                const bool walking = (int)node >= 0;
                 if (COUNT && __any(walking) && lane == 0) ++c_bstep;
                 if (COUNT && walking) ++c_blane;
                 if (walking) {
-                    // one 16-byte load per node: the quantised box and the link
-                    const uint4 n = __builtin_bit_cast(
-                        uint4, __builtin_amdgcn_raw_buffer_load_b128(qrs, (uint32_t)node * 16u, 0, 0));
-                    const bool leaf = (n.w & kQLeaf) != 0u;
-                    if (COUNT) ++c_box;
-                    const bool hit = qbox_hit(qray, n);
-                    // skip links point forward; max() keeps every walk finite
-                    const int next = leaf ? node + 1 : max((int)n.w, node + 1);
-                    node = (hit && !leaf) ? node + 1 : next;
-                    const uint32_t payload = n.w & ~kQLeaf;
-                    const bool take = hit && leaf;
-                    const bool first_free = p0 == 0u;
-                    p0 = (take && first_free) ? payload : p0;
-                    p1 = (take && !first_free) ? payload : p1;
-                }
-            }
-            const bool walk = node < n_total && p1 == 0u;
-            const bool stuck = p0 != 0u && !walk;
-            if (2 * __popcll(__ballot(stuck)) >= kBoxSwitch2 * __popcll(__ballot(walk))) break;
-        }
-        // triangle phase: one triangle of the first pending leaf per lane and
-        // step; it ends when no leaf is pending, or when lanes that could walk
-        // but hold no leaf outnumber the lanes testing
-        while (true) {
-            const bool test = p0 != 0u;
-            if (!__any(test)) break;
-            if (COUNT && lane == 0) ++c_tstep;
-            if (test) {
-                const uint32_t t = p0 >> 3;
-                bool h = false;
-                if (t < n_tris) {       // a payload past the triangle array tests nothing
-                    const float4* tv = reinterpret_cast<const float4*>(tri_bytes + t * 48u);
-                    if (COUNT) ++c_tri;
-                    h = tri_anyhit(ray, tv[0], tv[1], tv[2]);
-                }
-                if (h) {
-                    const uint32_t slot = tag >> 8;
-                    atomicOr(hitbits + (int64_t)(slot >> 5) * N + base_pix + (tag & 255u), 1u << (slot & 31));
-                    ++c_hits;
-                    active = false;
-                    node = n_total;
-                    p0 = p1 = 0u;
-                } else {
-                    p0 += 7u;
-                    if ((p0 & 7u) == 0u) {
-                        p0 = p1;
-                        p1 = 0u;
-                    }
-                }
-            }
-            const bool testing = p0 != 0u;
-            const bool idle = !testing && node < n_total;
-            if (2 * __popcll(__ballot(idle)) > kTriSwitch2 * __popcll(__ballot(testing))) break;
-        }
-        if (active && p0 == 0u && node >= n_total) active = false;  // miss
-    }
-    if (COUNT) {
-        const uint32_t h = wave_sum(c_hits), bx = wave_sum(c_box), tr = wave_sum(c_tri), bl = wave_sum(c_blane);
-        if (lane == 0) {
-            atomicAdd(&A.stats->box_lanes, (unsigned long long)bl);
-            atomicAdd(&A.stats->rays_hit, (unsigned long long)h);
-            atomicAdd(&A.stats->box_tests, (unsigned long long)bx);
-            atomicAdd(&A.stats->tri_tests, (unsigned long long)tr);
-            atomicAdd(&A.stats->box_slots, 64ull * c_bstep);
-            atomicAdd(&A.stats->tri_slots, 64ull * c_tstep);
-        }
-    }
-}
-
-// Pending references of the wide traversal, per lane, in LDS: entry k of
-// the workgroup's lane t at [k * kBlock + t] (lanes of a wave hit distinct
-// banks whatever their stack depths).  kStack entries, and four spare rows
-// for the stores of a visit that begins with a full stack (18 KB per
-// workgroup: eight workgroups per CU still fit).
-constexpr int kStack = 14, kStackRows = kStack + 4;
-
-template <bool COUNT>
-__device__ __forceinline__ void trace_tile_wide(const ShadeArgs& A, int64_t tile, const float4* R, int count,
-                                                uint32_t* hitbits, int* s_next, uint32_t* s_stack) {
-    const Scene& sc = A.scene;
-    const int64_t N = A.g.n;
-    const int64_t base_pix = tile * kBlock;
-    const int n_total = sc.nodes[0].escape;
-    const uint32_t n_tris = (uint32_t)sc.n_tris;
-    const QFrame F = *sc.frame;
-    const char* tri_bytes = reinterpret_cast<const char*>(sc.tris);
-    // nodes as buffer resources: 32-bit offsets, and a load past the end
-    // returns zeros instead of reading out of bounds
-    const __amdgpu_buffer_rsrc_t qrs = __builtin_amdgcn_make_buffer_rsrc(
-        (void*)sc.qnodes, (short)0, (int)((uint32_t)n_total * 16u), kBufferWord3);
-    const __amdgpu_buffer_rsrc_t grs = __builtin_amdgcn_make_buffer_rsrc(
-        (void*)sc.groups, (short)0, (int)sc.group_bytes, kBufferWord3);
-    const __amdgpu_buffer_rsrc_t ors = __builtin_amdgcn_make_buffer_rsrc(
-        (void*)sc.gorder, (short)0, (int)(sc.group_bytes / 16u), kBufferWord3);
-    uint32_t* stk = s_stack + threadIdx.x;
-    const int lane = __lane_id();
-    const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-    bool active = false, exhausted = false;
-    Ray ray;
-    QRay qray;
-    uint32_t oct3 = 0u;    // 3 x the ray's octant (bit a: negative on axis a)
-    // wide: node = a wide node, a leaf reference waiting for a pending slot,
-    // or kWideNone (done); binary (after a stack overflow): a node index, done
-    // at n_total
-    bool wide = false;
-    uint32_t node = (uint32_t)n_total;
-    int sp = 0;
-    // (every wide walk ends: the builder checked that each internal child
-    // reference is larger than its parent's index and smaller than the node
-    // count, and picks the binary walk for the scene otherwise)
-    uint32_t p0 = 0u, p1 = 0u;
-    uint32_t tag = 0u;     // the ray's pixel within the tile | sample slot << 8
-    uint32_t c_hits = 0, c_box = 0, c_tri = 0, c_bstep = 0, c_tstep = 0;   // steps: lane 0 only
-    uint32_t c_blane = 0;
-    // scheduling knobs: refill batch, node steps per phase check, and the
-    // phase hand-over ratios (in halves)
-    // (measured on the lattice: refills of 16 lanes, three visits per phase
-    // check and a triangle phase that yields only to twice as many idle
-    // walkers as testers take the walk from 31.9 to 29.8 ms; refills of 48
-    // lanes cost 13%; with the big-triangle subtree, a box phase that hands
-    // over once the lanes stuck on leaves are half as many as the walkers
-    // 11.9 -> 11.6 ms, and four visits per phase check 11.4 -> 11.1 ms)
-    constexpr int kRefillMin = 16, kBoxSteps = 4, kBoxSwitch2 = 1, kTriSwitch2 = 4;
-    auto walkable = [&]() { return (wide ? node != kWideNone : node < (uint32_t)n_total) && p1 == 0u; };
-    while (true) {
-        // refill when half of the wave is idle, or when nobody is busy
-        const uint64_t need = __ballot(!active && !exhausted);
-        const uint64_t busy = __ballot(active);
-        if (need && (__popcll(need) >= kRefillMin || busy == 0ull)) {
-            const int leader = __ffsll((unsigned long long)need) - 1;
-            int b = 0;
-            if (lane == leader) b = atomicAdd(s_next, (int)__popcll(need));
-            b = __shfl(b, leader);
-            if (!active && !exhausted) {
-                const int idx = b + (int)__popcll(need & lt);
-                if (idx < count) {
-                    const float4 rr = R[idx];
-                    tag = __float_as_uint(rr.w);
-                    const float4 o = A.origins[base_pix + (tag & 255u)];
-                    ray = make_ray(f3(o.x, o.y, o.z), f3(rr.x, rr.y, rr.z));
-                    qray = make_qray(ray, F);
-                    oct3 = 3u * ((rr.x < 0.0f ? 1u : 0u) | (rr.y < 0.0f ? 2u : 0u) | (rr.z < 0.0f ? 4u : 0u));
-                    wide = true;
-                    node = 0u;
-                    sp = 0;
-                    p0 = p1 = 0u;
-                    active = n_total > 0;
-                } else {
-                    exhausted = true;
-                }
-            }
-        }
-        if (!__any(active)) {
-            if (!__any(!exhausted)) break;
-            continue;
-        }
-        // box phase: a lane walks while its second leaf slot is free and the
-        // walk is not finished (a leaf found with the first slot taken goes
-        // to the second); the phase ends once the lanes that hold a leaf and
-        // cannot walk are at least as many as the lanes still walking
-        while (true) {
-            if (!__any(active && walkable())) break;
+                    // one wide node: four child records from one 64-byte
+                    // segment, in LDS when the node is hoisted
+                    uint4 c[4];
+                    if (node & kRefTop) {
 #pragma unroll
-            for (int step = 0; step < kBoxSteps; ++step) {
-                const bool walking = active && walkable();
-                if (COUNT && __any(walking) && lane == 0) ++c_bstep;
-                if (COUNT && walking) ++c_blane;
-                if (walking && wide) {
-                    if (node & kQLeaf) {
-                        // a leaf reference: to the free pending slot
-                        const uint32_t payload = node & ~kQLeaf;
-                        if (p0 == 0u) p0 = payload;
-                        else p1 = payload;
-                        node = sp > 0 ? (stk[--sp * kBlock] & ~kRefLive) : kWideNone;
+                        for (int k = 0; k < 4; ++k) c[k] = s_top[4u * (node & (kRefTop - 1u)) + k];
                     } else {
-                        // one wide node: four child records from one 64-byte
-                        // segment, and its visit order for the ray's octant
                         const uint32_t off = node * 64u;
-                        uint4 c[4];
 #pragma unroll
                         for (int k = 0; k < 4; ++k)
                             c[k] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(grs, off + 16u * k, 0, 0));
-                        const uint32_t f = (__builtin_amdgcn_raw_buffer_load_b32(ors, node * 4u, 0, 0) >> oct3) & 7u;
-                        // a missed child's reference becomes 0 (no kRefLive
-                        // bit: the push below does not keep it)
-                        uint32_t w[4];
-#pragma unroll
-                        for (int k = 0; k < 4; ++k) {
-                            if (COUNT && (c[k].w & ~kRefLive) != kQLeaf) ++c_box;
-                            w[k] = qbox_hit(qray, c[k]) ? c[k].w : 0u;
-                        }
-                        // farther child of each split after the nearer one
-                        // (the pushed-last is popped first): within each pair,
-                        // then the pairs
-                        const bool s0 = (f & 1u) != 0u, s1 = (f & 2u) != 0u, sT = (f & 4u) != 0u;
-                        const uint32_t a0 = s0 ? w[1] : w[0], a1 = s0 ? w[0] : w[1];
-                        const uint32_t a2 = s1 ? w[3] : w[2], a3 = s1 ? w[2] : w[3];
-                        const uint32_t ws[4] = {sT ? a2 : a0, sT ? a3 : a1, sT ? a0 : a2, sT ? a1 : a3};
-                        // every hit child is pushed: each record is stored at
-                        // the first free row and the row is kept if the child
-                        // was hit (rows up to kStack + 3 exist, so a visit
-                        // starting with a full stack stays in bounds; the
-                        // overflow is checked once per visit); then the top is
-                        // popped as the next node
-                        int row = sp;
-#pragma unroll
-                        for (int k = 0; k < 4; ++k) {
-                            stk[row * kBlock] = ws[k];
-                            row += (int)((ws[k] & kRefLive) >> 30);
-                        }
-                        sp = row;
-                        const bool over = sp > kStack;
-                        const uint32_t top = stk[(sp > 0 ? sp - 1 : 0) * kBlock] & ~kRefLive;
-                        const uint32_t next = sp > 0 ? top : kWideNone;
-                        sp = sp > 0 ? sp - 1 : 0;
-                        node = next;
-                        if (!over && next != kWideNone && (next & kQLeaf)) {
-                            // a leaf reference on top goes to a pending slot
-                            // now (this visit started with the second free),
-                            // and the next entry is popped
-                            const uint32_t payload = next & ~kQLeaf;
-                            if (p0 == 0u) p0 = payload;
-                            else p1 = payload;
-                            node = sp > 0 ? (stk[--sp * kBlock] & ~kRefLive) : kWideNone;
-                        }
-                        if (over) {
-                            // the stack is full: walk the binary tree from the
-                            // root instead (the same answer, more steps)
-                            wide = false;
-                            node = 0u;
-                            sp = 0;
-                        }
                     }
-                } else if (walking) {
-                    // binary pre-order walk with skip links: one 16-byte node
-                    const uint4 n = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(qrs, node * 16u, 0, 0));
-                    const bool leaf = (n.w & kQLeaf) != 0u;
-                    if (COUNT) ++c_box;
-                    const bool hit = qbox_hit(qray, n);
-                    // skip links point forward; max() keeps every walk finite
-                    const uint32_t next = leaf ? node + 1u : max(n.w, node + 1u);
-                    node = (hit && !leaf) ? node + 1u : next;
-                    const uint32_t payload = n.w & ~kQLeaf;
-                    const bool take = hit && leaf;
-                    const bool first_free = p0 == 0u;
-                    p0 = (take && first_free) ? payload : p0;
-                    p1 = (take && !first_free) ? payload : p1;
+                    // a missed child's reference becomes 0 (no kRefLive
+                    // bit: the push below does not keep it)
+                    uint32_t w[4];
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) {
+                        if (COUNT && (c[k].w & kRefMask) != kEmptyRef) ++c_box;
+                        w[k] = qbox_hit(qray, c[k]) ? c[k].w : 0u;
+                    }
+                    // farther child of each split after the nearer one
+                    // (the pushed-last is popped first): within each pair,
+                    // then the pairs
+                    const bool s0 = split_swaps(oct, c[1].w), s1 = split_swaps(oct, c[2].w),
+                               sT = split_swaps(oct, c[0].w);
+                    const uint32_t a0 = s0 ? w[1] : w[0], a1 = s0 ? w[0] : w[1];
+                    const uint32_t a2 = s1 ? w[3] : w[2], a3 = s1 ? w[2] : w[3];
+                    const uint32_t ws[4] = {sT ? a2 : a0, sT ? a3 : a1, sT ? a0 : a2, sT ? a1 : a3};
+                    // every hit child is pushed: each record is stored at
+                    // the first free row and the row is kept if the child
+                    // was hit; then the top is popped as the next node
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) {
+                        row(sp) = ws[k];
+                        sp += ((ws[k] >> 30) & 1u) * kRow;
+                    }
+                    if (sp > sp_end) restart = true;
+                    sp -= kRow;
+                    node = row(sp) & kRefMask;
+                    // a leaf on top goes to the pending slot if that is free,
+                    // and the next entry is popped
+                    if (p0 == 0u && (int)node < 0 && node != kWideNone) {
+                        p0 = node;
+                        sp -= kRow;
+                        node = row(sp) & kRefMask;
+                    }
+                    if (restart) node = kWideNone;
                 }
             }
-            const bool walk = active && walkable();
-            const bool stuck = p0 != 0u && !walk;
-            if (2 * __popcll(__ballot(stuck)) >= kBoxSwitch2 * __popcll(__ballot(walk))) break;
+            if (__any(restart)) {
+                // the stack was full: these rays walk the binary tree from
+                // the root instead (the same answer, more steps)
+                if (restart) {
+                    uint32_t nb = 0, nt = 0;
+                    if (qbvh_anyhit<COUNT>(sc, ray, qray, n_total, nb, nt)) report();
+                    c_box += nb;
+                    c_tri += nt;
+                    restart = false;
+                    node = kWideNone;
+                    p0 = 0u;
+                }
+            }
+            const uint64_t walk = __ballot((int)node >= 0);
+            if (walk == 0ull) break;
+            const uint64_t stuck = __ballot(p0 != 0u && (int)node < 0);
+            if (4 * __popcll(stuck) >= kBoxSwitch4 * __popcll(walk)) break;
         }
-        // triangle phase: one triangle of the first pending leaf per lane and
-        // step; it ends when no leaf is pending, or when lanes that could walk
-        // but hold no leaf outnumber the lanes testing
+        // triangle phase: one triangle of the pending leaf per lane and step;
+        // it ends when no leaf is pending, or when lanes that could walk but
+        // hold no leaf outnumber the lanes testing
         while (true) {
             const bool test = p0 != 0u;
             if (!__any(test)) break;
             if (COUNT && lane == 0) ++c_tstep;
             if (test) {
-                const uint32_t t = p0 >> 3;
+                const uint32_t t = (p0 >> 2) & 0x03FFFFFFu;
                 bool h = false;
-                if (t < n_tris) {       // a payload past the triangle array tests nothing
-                    const float4* tv = reinterpret_cast<const float4*>(tri_bytes + t * 48u);
+                if (t < n_tris) {       // a reference past the triangle array tests nothing
                     if (COUNT) ++c_tri;
-                    h = tri_anyhit(ray, tv[0], tv[1], tv[2]);
+                    h = tri_anyhit(ray, tri_bytes + t * 48u);
                 }
                 if (h) {
-                    const uint32_t slot = tag >> 8;
-                    atomicOr(hitbits + (int64_t)(slot >> 5) * N + base_pix + (tag & 255u), 1u << (slot & 31));
-                    ++c_hits;
-                    active = false;
-                    wide = false;
-                    node = (uint32_t)n_total;
-                    sp = 0;
-                    p0 = p1 = 0u;
+                    report();
+                    node = kWideNone;
+                    p0 = 0u;
+                } else if ((p0 & 3u) != 0u) {
+                    p0 += 3u;
                 } else {
-                    p0 += 7u;
-                    if ((p0 & 7u) == 0u) {
-                        p0 = p1;
-                        p1 = 0u;
+                    p0 = 0u;
+                    if ((int)node < 0 && node != kWideNone) {   // the leaf that waited
+                        p0 = node;
+                        sp -= kRow;
+                        node = row(sp) & kRefMask;
                     }
                 }
             }
-            const bool testing = p0 != 0u;
-            const bool idle = !testing && active && walkable();
-            if (2 * __popcll(__ballot(idle)) > kTriSwitch2 * __popcll(__ballot(testing))) break;
+            const uint64_t testing = __ballot(p0 != 0u);
+            const uint64_t free_ = __ballot(p0 == 0u && (int)node >= 0);
+            if (2 * __popcll(free_) > kTriSwitch2 * __popcll(testing)) break;
         }
-        if (active && p0 == 0u && !(wide ? node != kWideNone : node < (uint32_t)n_total)) active = false;  // miss
+        if (exhausted && !__any(node != kWideNone || p0 != 0u)) break;
     }
     if (COUNT) {
         const uint32_t h = wave_sum(c_hits), bx = wave_sum(c_box), tr = wave_sum(c_tri), bl = wave_sum(c_blane);
@@ -807,14 +663,6 @@ __device__ __forceinline__ void trace_tile_wide(const ShadeArgs& A, int64_t tile
             atomicAdd(&A.stats->tri_slots, 64ull * c_tstep);
         }
     }
-}
-
-// The walk the scene's builder chose (a uniform branch: one scalar load).
-template <bool COUNT>
-__device__ __forceinline__ void trace_tile(const ShadeArgs& A, int64_t tile, const float4* R, int count,
-                                           uint32_t* hitbits, int* s_next, uint32_t* s_stack) {
-    if (A.scene.info->wide) trace_tile_wide<COUNT>(A, tile, R, count, hitbits, s_next, s_stack);
-    else trace_tile_binary<COUNT>(A, tile, R, count, hitbits, s_next);
 }
 
 // 3) evaluation: forward values or the adjoint, from the hit bits.  For the
@@ -1069,13 +917,15 @@ __global__ __launch_bounds__(1024) void order_tiles_kernel(const int32_t* __rest
     }
 }
 
-// eight waves per SIMD (the hardware's limit): 64 registers per lane.
+// eight waves per SIMD (the hardware's limit): 64 registers per lane, 20 KB
+// of LDS per workgroup.
 // Workgroup b traces part b % parts of the b / parts-th tile's rays.
 template <bool COUNT>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8))) void trace_rays_kernel(
     ShadeArgs A, uint32_t* hitbits, int parts) {
     __shared__ int s_next;
     __shared__ uint32_t s_stack[kStackRows * kBlock];
+    __shared__ uint4 s_top[4 * kTopNodes];
     const int rank = (int)blockIdx.x / parts, part = (int)blockIdx.x - rank * parts;
     const int64_t tile = A.tile_order ? A.tile_order[rank] : rank;
     if (tile < 0 || tile >= (int64_t)gridDim.x / parts) return;   // uniform: the whole workgroup reads the same entry
@@ -1084,7 +934,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8))) voi
     if (first >= all) return;
     if (threadIdx.x == 0) s_next = 0;
     __syncthreads();
-    trace_tile<COUNT>(A, tile, tile_region(A, tile) + first, min(chunk, all - first), hitbits, &s_next, s_stack);
+    trace_tile<COUNT>(A, tile, tile_region(A, tile) + first, min(chunk, all - first), hitbits, &s_next, s_stack,
+                      s_top);
 }
 
 template <bool BWD, bool DUMP, bool BIL>
@@ -1142,6 +993,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     extern __shared__ float smem[];
     __shared__ int s_tile, s_item, s_cnt, s_next;
     __shared__ uint32_t s_stack[kStackRows * kBlock];
+    __shared__ uint4 s_top[4 * kTopNodes];
     float* s_hot = smem;                     // 3 * kHotMax
     float* s_marg = smem + 3 * kHotMax;      // H + 1 of the current item
     float4* region = scratch + (size_t)blockIdx.x * (size_t)(2 * spp_max * kBlock);
@@ -1169,7 +1021,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
         float4* reg = A.tau != 0.0f ? region : nullptr;
         gen_tile<false>(A, tile, reg, it.hitbits, s_marg, &s_cnt);
         __syncthreads();
-        if (reg) trace_tile<false>(A, tile, reg, s_cnt, it.hitbits, &s_next, s_stack);
+        if (reg) trace_tile<false>(A, tile, reg, s_cnt, it.hitbits, &s_next, s_stack, s_top);
         __syncthreads();
         const bool bil = (A.flags & MCDI_FLAG_BILINEAR) != 0;
         if (bil) shade_tile<false, false, true, false, true>(A, tile, s_marg, s_hot, RecSink{nullptr, nullptr});
@@ -1197,7 +1049,7 @@ __global__ void trace_kernel(Scene sc, const float* o, const float* d, int64_t n
     bool h;
     if (brute == 1) h = brute_anyhit(sc, r);
     else if (brute == 2) h = wbvh_anyhit(sc, r, n_total, nb, nt);
-    else h = qbvh_anyhit(sc, r, n_total, nb, nt);
+    else h = qbvh_anyhit(sc, r, make_qray(r, *sc.frame), n_total, nb, nt);
     hit[k] = h ? 1 : 0;
 }
 
@@ -1208,12 +1060,13 @@ static unsigned n_blocks(const ShadeArgs& a) { return (unsigned)((a.g.n + kBlock
 // Workgroups that share one tile's rays in the traversal.  256 CUs hold 2048
 // of its workgroups; a launch with fewer tiles leaves CUs idle while each
 // lane walks up to 2 spp rays one after another, so its tiles are split until
-// they fill the chip once, at most down to one ray per lane.  Measured
-// (traversal, one part against this rule): 16 tiles at 4 spp 137 -> 45 us,
-// 382 tiles at 8 spp 398 -> 150 us, 1572 tiles at 16 spp 883 -> 545 us; filling
-// the chip twice or four times over gives 189 and 235 us at 382 tiles, and
-// splitting launches that fill it already costs (8192 tiles at 12 spp: 2.36 ms
-// whole, 2.51 in halves; 16384 tiles at 32 spp: 10.6 whole, 11.1 in halves).
+// they fill the chip once, at most down to one ray per lane.  Measured when
+// the rule was made (traversal, one part against this rule): 16 tiles at 4 spp
+// 137 -> 45 us, 382 tiles at 8 spp 398 -> 150 us, 1572 tiles at 16 spp 883 ->
+// 545 us; filling the chip twice or four times over gives 189 and 235 us at
+// 382 tiles, and splitting launches that fill it already costs (8192 tiles at
+// 12 spp: 2.36 ms whole, 2.51 in halves; 16384 tiles at 32 spp: 10.6 whole,
+// 11.1 in halves).
 static int trace_parts(const ShadeArgs& a) {
     constexpr unsigned kSlots = 2048;
     const unsigned tiles = n_blocks(a), most = 2u * (unsigned)a.spp;
