@@ -158,6 +158,115 @@ __global__ __launch_bounds__(256) void morton(const float4* tmp, int64_t nt, con
     if ((threadIdx.x & 63) == 0 && m != 0) atomicAdd(&info->n_big, (int)__popcll(m));
 }
 
+// The big triangles' subtree by the surface area heuristic (one workgroup,
+// after the sort; at most kBigSah of them, beyond that they keep their Morton
+// keys).  Every shadow ray of a scene with walls walks this subtree first, and
+// under the Morton order one wall's triangles are spread over several nodes
+// whose boxes span the room.  The split of least cost (areas times counts over
+// every triangle's centroid as the plane, all three axes) is found level by
+// level for all nodes at once, and a triangle's path is written into its key
+// as the radix tree reads it: each level takes the next bit down whose place
+// stands for the split's axis, set for the upper side.  Paths that run out of
+// bits, and equal centroids, are split by index as equal keys are.
+// 36 walls of a room of 1.0M triangles: 6.1 -> 4.6 node visits a shadow ray
+// (studied on the CPU), shadow rays 7.1 -> 5.4 ms.
+constexpr int kBigSah = 128;
+__global__ __launch_bounds__(3 * kBigSah) void big_sah(const float4* tmp, int nt, uint64_t* keys, uint32_t* vals,
+                                                       const DeviceSceneInfo* info) {
+    __shared__ float lo[3][kBigSah], hi[3][kBigSah], ctr[3][kBigSah];
+    __shared__ unsigned long long code[kBigSah], best[kBigSah];
+    __shared__ int s_more;
+    const int n = info->n_big;
+    if (n < 3 || n > kBigSah || n >= nt) return;
+    const int i = threadIdx.x % kBigSah, axis = threadIdx.x / kBigSah;
+    const bool own = axis == 0 && i < n;      // one thread of each triangle
+    uint32_t val = 0;
+    if (own) {
+        val = vals[i];
+        const float4* t = tmp + 3 * (size_t)val;
+        const float v[3][3] = {{t[0].x, t[1].x, t[2].x}, {t[0].y, t[1].y, t[2].y}, {t[0].z, t[1].z, t[2].z}};
+        for (int a = 0; a < 3; ++a) {
+            lo[a][i] = fminf(v[a][0], fminf(v[a][1], v[a][2]));
+            hi[a][i] = fmaxf(v[a][0], fmaxf(v[a][1], v[a][2]));
+            ctr[a][i] = (v[a][0] + v[a][1] + v[a][2]) * (1.0f / 3.0f);
+        }
+        code[i] = 0ull;
+    }
+    int bit = 62;          // the node's next key bit (the same for all its triangles)
+    bool open = true;      // the node may still be split
+    __syncthreads();
+    for (int level = 0; level < 63; ++level) {
+        // the node's first triangle stands for it
+        int rep = i;
+        if (i < n) {
+            const unsigned long long c = code[i];
+            for (int j = i - 1; j >= 0; --j) rep = code[j] == c ? j : rep;
+            if (own) best[i] = ~0ull;
+        }
+        if (threadIdx.x == 0) s_more = 0;
+        __syncthreads();
+        if (i < n && open) {
+            const unsigned long long c = code[i];
+            const float at = ctr[axis][i];
+            float bl[2][3], bh[2][3];
+            int cnt[2] = {0, 0};
+            for (int s = 0; s < 2; ++s)
+                for (int a = 0; a < 3; ++a) {
+                    bl[s][a] = INFINITY;
+                    bh[s][a] = -INFINITY;
+                }
+            for (int j = 0; j < n; ++j) {
+                if (code[j] != c) continue;
+                const int s = ctr[axis][j] > at ? 1 : 0;
+                for (int q = 0; q < 2; ++q) {
+                    if (q != s) continue;
+                    ++cnt[q];
+                    for (int a = 0; a < 3; ++a) {
+                        bl[q][a] = fminf(bl[q][a], lo[a][j]);
+                        bh[q][a] = fmaxf(bh[q][a], hi[a][j]);
+                    }
+                }
+            }
+            if (cnt[1] > 0) {
+                float cost = 0.0f;
+                for (int s = 0; s < 2; ++s) {
+                    const float dx = bh[s][0] - bl[s][0], dy = bh[s][1] - bl[s][1], dz = bh[s][2] - bl[s][2];
+                    cost += (dx * dy + dy * dz + dz * dx) * (float)cnt[s];
+                }
+                if (cost >= 0.0f)
+                    atomicMin(&best[rep], ((unsigned long long)__float_as_uint(cost) << 32) |
+                                              (unsigned long long)(axis << 8 | i));
+            }
+        }
+        __syncthreads();
+        if (i < n && open) {
+            const unsigned long long b = best[rep];
+            const int a = (int)(b >> 8) & 3, pivot = (int)(b & 255u);
+            int at = bit;
+            if (b != ~0ull)
+                while (at >= 0 && 2 - at % 3 != a) --at;
+            open = b != ~0ull && at >= 0;
+            if (open) {
+                if (own) {
+                    s_more = 1;
+                    if (ctr[a][i] > ctr[a][pivot]) code[i] |= 1ull << at;
+                }
+                bit = at - 1;
+            }
+        }
+        __syncthreads();
+        if (!s_more) break;       // uniform: written before the barrier, cleared after the next one
+        __syncthreads();
+    }
+    if (own) {
+        const unsigned long long c = code[i];
+        int rank = 0;
+        for (int j = 0; j < n; ++j) rank += (code[j] < c || (code[j] == c && j < i)) ? 1 : 0;
+        keys[rank] = c;
+        vals[rank] = val;
+    }
+}
+
 struct Tree {
     int32_t* parent;   // [2nt-1]
     int32_t* left;     // [nt-1] node ids (leaf k = nt-1+k)
@@ -828,6 +937,7 @@ hipError_t build_bvh(const float* verts, int64_t nv, const int32_t* tris, int64_
         hipLaunchKernelGGL(morton, dim3(nblk(nt)), dim3(256), 0, s, tmp, (int64_t)nt, cb, keys, vals, info);
         err = rocprim::radix_sort_pairs(sort_tmp, sort_bytes, keys, keys2, vals, vals2, (size_t)nt, 0, 64, s);
         if (err == hipSuccess) {
+            hipLaunchKernelGGL(big_sah, dim3(1), dim3(3 * kBigSah), 0, s, tmp, nt, keys2, vals2, info);
             hipLaunchKernelGGL(fill_i32, dim3(nblk(2 * nt - 1)), dim3(256), 0, s, T.parent, (int64_t)(2 * nt - 1), -1);
             hipLaunchKernelGGL(fill_i32, dim3(nblk(2 * nt - 1)), dim3(256), 0, s, T.cnt, (int64_t)(2 * nt - 1), 0);
             hipLaunchKernelGGL(fill_i32, dim3(nblk(nt)), dim3(256), 0, s, T.mark, (int64_t)nt, 0);

@@ -451,7 +451,7 @@ __device__ __forceinline__ void gen_tile(const ShadeArgs& A, int64_t tile, float
 //    binary nodes after the visits of the step.
 //    Shadow rays, before (two walks in the loop, a separate order word, two
 //    pending leaves, no hoisted nodes) -> after: 4.2M pixels at 32 spp in the
-//    room 10.6 -> 7.1 ms, 1.05M pixels at
+//    room 10.6 -> 7.1 ms (5.4 with the big triangles' SAH subtree), 1.05M pixels at
 //    12 spp on a 102k-triangle surface 2.36 -> 1.70 ms, 201k pixels at 16 spp
 //    on a 45k-triangle one 545 -> 385 us, 4096 pixels at 4 spp 45 -> 30 us.
 //

@@ -1,7 +1,8 @@
 """The shading path's shadow rays at the edges of the traversal's rules, hit
 bits against brute force: launches whose tiles are shared by several
 workgroups (one pixel, parts of one wavefront, ragged last tiles, one tile
-fewer and more than fill the chip), and meshes around the number of hoisted nodes."""
+fewer and more than fill the chip), meshes around the number of hoisted nodes,
+and scenes with few and many big triangles."""
 
 import numpy as np
 import pytest
@@ -68,3 +69,11 @@ def _soup(nt, size, seed):
 def test_mesh_sizes(nt):
     v, f = _soup(nt, 0.05, nt)
     _check(v, f, make_workload("tiny").env, 3000, 3, nt)
+
+
+@pytest.mark.parametrize("n_big", [1, 2, 3, 36, 127, 128, 129, 200])
+def test_big_triangles(n_big):
+    v, f = _soup(500, 0.02, n_big)
+    bv, bf = _soup(n_big, 0.8, n_big + 1)
+    info = _check(np.concatenate([v, bv]), np.concatenate([f, bf + len(v)]), make_workload("tiny").env, 3000, 3, n_big)
+    assert info["n_big"] >= n_big * 0.8
