@@ -184,7 +184,7 @@ struct mcdi_env_s {
     float* cond = nullptr;
     float* marg = nullptr;
     float* pdf = nullptr;
-    double* rowsum = nullptr;  // [H + 1]
+    double* rowsum = nullptr;  // [2 H + 1]
     int32_t* light = nullptr;
     int32_t* hot_slot = nullptr;   // [H*W]
     int32_t* hot_texel = nullptr;  // [kHotMax]
@@ -327,7 +327,7 @@ mcdi_status mcdi_build_env_cdf(const float* env_rgb, int32_t H, int32_t W, const
     ev->cond = (float*)ev->alloc.get(sizeof(float) * ((size_t)H * (W + 1) + 16), s);
     ev->marg = (float*)ev->alloc.get(sizeof(float) * (size_t)(H + 1), s);
     ev->pdf = (float*)ev->alloc.get(sizeof(float) * (size_t)H * W, s);
-    ev->rowsum = (double*)ev->alloc.get(sizeof(double) * (size_t)(H + 1), s);
+    ev->rowsum = (double*)ev->alloc.get(sizeof(double) * (size_t)(2 * H + 1), s);
     ev->light = (int32_t*)ev->alloc.get(sizeof(int32_t), s);
     ev->hot_slot = (int32_t*)ev->alloc.get(sizeof(int32_t) * (size_t)H * W, s);
     ev->hot_texel = (int32_t*)ev->alloc.get(sizeof(int32_t) * kHotMax, s);
@@ -342,11 +342,9 @@ mcdi_status mcdi_build_env_cdf(const float* env_rgb, int32_t H, int32_t W, const
         mcdi_destroy_env(ev);
         return fail(MCDI_E_OOM, "mcdi_build_env_cdf: device allocation failed");
     }
-    hipError_t e = launch_env_cdf(env_rgb, H, W, ev->cond, ev->marg, ev->pdf, ev->rowsum, ev->light, s);
-    if (e == hipSuccess) e = launch_env_guide(ev->cond, H, W, ev->G, ev->guide, s);
-    if (e == hipSuccess) e = launch_env_pack(env_rgb, ev->pdf, (int64_t)H * W, ev->tex, s);
-    if (e == hipSuccess) e = launch_env_dclass(ev->pdf, (int64_t)H * W, ev->dclass, s);
-    if (e == hipSuccess) e = launch_env_hot(ev->pdf, H, W, ev->hot_slot, ev->hot_texel, ev->n_hot, s);
+    const EnvTables t{ev->cond, ev->marg, ev->pdf, ev->rowsum, ev->light, ev->guide, ev->G, ev->tex, ev->dclass,
+                      ev->hot_slot, ev->hot_texel, ev->n_hot};
+    const hipError_t e = launch_env_tables(env_rgb, H, W, t, s);
     if (e != hipSuccess) {
         mcdi_destroy_env(ev);
         return fail(MCDI_E_DEVICE, "mcdi_build_env_cdf: %s", hipGetErrorString(e));

@@ -208,21 +208,24 @@ struct ServeItem {
 // kernel launchers (return hipError_t of the launch)
 hipError_t launch_serve(const ServeItem* items_dev, int n_items, int64_t total_tiles, int* tile_counter,
                         float4* scratch, int spp_max, int n_workgroups, int max_H, hipStream_t s);
-hipError_t launch_env_cdf(const float* env, int H, int W, float* cond, float* marg, float* pdf,
-                          double* rowsum, int32_t* light_enabled, hipStream_t s);
+// the probe's tables, in one build (all buffers the handle's)
+struct EnvTables {
+    float *cond, *marg, *pdf;
+    double* rowsum;            // [2 H + 1] scratch: row sums, the total, the rows' sines
+    int32_t* light_enabled;
+    int32_t* guide;
+    int32_t G;
+    float4* tex;
+    uint8_t* dclass;
+    int32_t *hot_slot, *hot_texel, *n_hot;
+};
+hipError_t launch_env_tables(const float* env, int H, int W, const EnvTables& t, hipStream_t s);
 // Search guide of the conditional CDF rows: guide[i][g] = the largest column
 // k <= W-1 with cond[i][k] <= g / G, for g = 0..G.
 int env_row_window(int H, int W);
 int env_guide_cells(int W, int win);
-// (r, g, b, pdf) per texel, after the tables
-hipError_t launch_env_pack(const float* env, const float* pdf, int64_t n, float4* tex, hipStream_t s);
 // out[k] = (rgb[k].xyz, dens[k].w)
 hipError_t launch_env_mix(const float4* rgb, const float4* dens, int64_t n, float4* out, hipStream_t s);
-hipError_t launch_env_guide(const float* cond, int H, int W, int G, int32_t* guide, hipStream_t s);
-// density classes of the texels, 2 bits each, 4 to a byte (dclass_kernel)
-hipError_t launch_env_dclass(const float* pdf, int64_t n, uint8_t* dclass, hipStream_t s);
-hipError_t launch_env_hot(const float* pdf, int H, int W, int32_t* hot_slot, int32_t* hot_texel, int32_t* n_hot,
-                          hipStream_t s);
 // forward = gen_rays -> trace_rays -> shade; hit bits are produced by the
 // first two and read by the third
 hipError_t launch_gen_rays(const ShadeArgs& a, uint32_t* hitbits, hipStream_t s);
