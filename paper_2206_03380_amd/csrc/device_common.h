@@ -163,6 +163,17 @@ __device__ __forceinline__ float smith_lambda(float t2, float a2) {
 // 50 instructions against 80.  Shadow rays of a room of 1.0M triangles 9.6 ->
 // 8.8 ms, of a 102k-triangle surface 2.26 -> 2.12 ms.
 //
+// Rays that graze an edge are decided by the last bit of the sheared
+// coordinates, so their rounding is part of the answer: row . (v - o) is
+// summed over x, y, z with y's product rounded and the other two fused.  A row
+// holds a one, a zero and -s (at kz), so the sum has one rounding where kz = z
+// and on the row of y where kz = x, and elsewhere two (the product's first).
+// A ray's (c, e) = (-s, 1) or (-1, s) gives either by one multiply and one FMA,
+// c (e z) + x: the product with a one is exact.
+//
+// Loads go by 32-bit byte offsets from the first triangle (below 2^26 triangles
+// of 48 bytes): 64-bit addresses cost two registers and spilled the walk.
+//
 // kx and ky stay in cyclic order when d[kz] < 0 (the published test swaps
 // them to keep the winding): the swap negates U, V, W, their sum and T exactly,
 // and a hit from either side counts.
@@ -172,7 +183,8 @@ struct Ray {
     float3 inv;      // 1/d (zero components replaced, boxes only)
     float3 clo, chi; // slab offsets for the low and high box corners (box_hit)
     float3 p;        // o[kx], o[ky], o[kz]
-    float sx, sy;    // d[kx] / d[kz], d[ky] / d[kz]
+    float cx, ex;    // shear of row kx, s = d[kx] / d[kz]: (-s, 1) where s z is fused into the sum, (-1, s) where rounded
+    float cy, ey;    // the same of row ky
     float sz;        // 1/d[kz]
     uint32_t rx, ry, rz;   // byte offsets of the rows kx, ky, kz
 };
@@ -206,8 +218,12 @@ __device__ __forceinline__ Ray make_ray(float3 o, float3 d) {
     const int ky = kx == 2 ? 0 : kx + 1;
     const float rz = fast_rcp(comp(d, kz));
     r.p = f3(comp(o, kx), comp(o, ky), comp(o, kz));
-    r.sx = comp(d, kx) * rz;
-    r.sy = comp(d, ky) * rz;
+    const float sx = comp(d, kx) * rz, sy = comp(d, ky) * rz;
+    const bool fx = kz != 1, fy = kz == 2;   // row kx = y at kz = x; both at kz = z
+    r.cx = fx ? -sx : -1.0f;
+    r.ex = fx ? 1.0f : sx;
+    r.cy = fy ? -sy : -1.0f;
+    r.ey = fy ? 1.0f : sy;
     r.sz = rz;
     r.rx = 16u * (uint32_t)kx;
     r.ry = 16u * (uint32_t)ky;
@@ -221,16 +237,16 @@ __device__ __forceinline__ Ray make_ray(float3 o, float3 d) {
     return r;
 }
 
-__device__ __forceinline__ bool tri_anyhit(const Ray& r, const void* tri) {
+__device__ __forceinline__ bool tri_anyhit(const Ray& r, const void* tris, uint32_t at) {
 #pragma clang fp contract(off)
-    const char* t = static_cast<const char*>(tri);
-    const float4 vx = *reinterpret_cast<const float4*>(t + r.rx);
-    const float4 vy = *reinterpret_cast<const float4*>(t + r.ry);
-    const float4 vz = *reinterpret_cast<const float4*>(t + r.rz);
+    const char* t = static_cast<const char*>(tris);
+    const float4 vx = *reinterpret_cast<const float4*>(t + (at + r.rx));
+    const float4 vy = *reinterpret_cast<const float4*>(t + (at + r.ry));
+    const float4 vz = *reinterpret_cast<const float4*>(t + (at + r.rz));
     const float az = vz.x - r.p.z, bz = vz.y - r.p.z, cz = vz.z - r.p.z;
-    const float Ax = (vx.x - r.p.x) - r.sx * az, Ay = (vy.x - r.p.y) - r.sy * az;
-    const float Bx = (vx.y - r.p.x) - r.sx * bz, By = (vy.y - r.p.y) - r.sy * bz;
-    const float Cx = (vx.z - r.p.x) - r.sx * cz, Cy = (vy.z - r.p.y) - r.sy * cz;
+    const float Ax = fmaf(r.cx, r.ex * az, vx.x - r.p.x), Ay = fmaf(r.cy, r.ey * az, vy.x - r.p.y);
+    const float Bx = fmaf(r.cx, r.ex * bz, vx.y - r.p.x), By = fmaf(r.cy, r.ey * bz, vy.y - r.p.y);
+    const float Cx = fmaf(r.cx, r.ex * cz, vx.z - r.p.x), Cy = fmaf(r.cy, r.ey * cz, vy.z - r.p.y);
     float U = Cx * By - Cy * Bx;
     float V = Ax * Cy - Ay * Cx;
     float W = Bx * Ay - By * Ax;
@@ -323,7 +339,7 @@ __device__ __forceinline__ bool leaf_anyhit(const Scene& sc, const Ray& r, uint3
     const uint32_t first = (ref >> 2) & 0x03FFFFFFu, cnt = (ref & 3u) + 1u;
     for (uint32_t k = first; k < first + cnt && k < (uint32_t)sc.n_tris; ++k) {
         if (COUNT) ++n_tri;
-        if (tri_anyhit(r, sc.tris + 3 * (size_t)k)) return true;
+        if (tri_anyhit(r, sc.tris, 48u * k)) return true;
     }
     return false;
 }
@@ -428,7 +444,7 @@ __device__ __forceinline__ bool bvh_anyhit(const Scene& sc, const Ray& r, int n_
         const int cnt = (first + (payload & 7) <= sc.n_tris) ? (payload & 7) : 0;
         for (int k = 0; k < cnt; ++k) {
             if (COUNT) ++n_tri;
-            if (tri_anyhit(r, sc.tris + 3 * (size_t)(first + k))) return true;
+            if (tri_anyhit(r, sc.tris, 48u * (uint32_t)(first + k))) return true;
         }
         i = next;
     }
@@ -437,7 +453,7 @@ __device__ __forceinline__ bool bvh_anyhit(const Scene& sc, const Ray& r, int n_
 
 __device__ __forceinline__ bool brute_anyhit(const Scene& sc, const Ray& r) {
     for (int64_t k = 0; k < sc.n_tris; ++k) {
-        if (tri_anyhit(r, sc.tris + 3 * k)) return true;
+        if (tri_anyhit(r, sc.tris, 48u * (uint32_t)k)) return true;
     }
     return false;
 }

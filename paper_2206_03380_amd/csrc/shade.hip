@@ -475,7 +475,6 @@ __device__ __forceinline__ void trace_tile(const ShadeArgs& A, int64_t tile, con
     // a hierarchy that failed the builder's check (never for a valid tree):
     // every ray walks the binary nodes
     const bool flat = sc.info->wide_bad != 0;
-    const char* tri_bytes = reinterpret_cast<const char*>(sc.tris);
     // nodes as a buffer resource: 32-bit offsets, and a load past the end
     // returns zeros instead of reading out of bounds
     const __amdgpu_buffer_rsrc_t grs = __builtin_amdgcn_make_buffer_rsrc(
@@ -629,7 +628,7 @@ __device__ __forceinline__ void trace_tile(const ShadeArgs& A, int64_t tile, con
                 bool h = false;
                 if (t < n_tris) {       // a reference past the triangle array tests nothing
                     if (COUNT) ++c_tri;
-                    h = tri_anyhit(ray, tri_bytes + t * 48u);
+                    h = tri_anyhit(ray, sc.tris, t * 48u);
                 }
                 if (h) {
                     report();
