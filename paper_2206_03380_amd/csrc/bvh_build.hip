@@ -9,16 +9,20 @@
 // leaves, and a final pass that writes every surviving node at its depth-first
 // pre-order index with a skip link, so traversal needs no stack.
 //
-// Fitting runs in two parts over blocks of 256 sorted triangles.  Nodes whose
-// triangles lie in one block are fitted bottom-up inside that block's
-// workgroup (workgroup-scope atomics pick the second child to arrive).  A
-// node spanning blocks is fitted directly: its box is the union of a suffix
-// box of its first block, a prefix box of its last block and a sparse-table
-// query over the whole blocks between (min and max are idempotent, so two
-// overlapping power-of-two ranges cover the span), and its surviving-node
-// count is 2 L - 1 for the L leaves in its range, read from a prefix sum of
-// leaf marks (every surviving internal node has two surviving children).  No
-// dependency chain crosses workgroups.
+// Fitting has no dependency chain: every internal node's box is a range of the
+// sorted triangles' boxes, found by two overlapping power-of-two ranges of a
+// sparse table (min and max are idempotent).  Blocks of 256 triangles hold
+// their table in LDS and fit the nodes inside them; super-blocks of 256 blocks
+// do the same with the blocks' boxes, and one table holds the super-blocks'.
+// A node spanning blocks is the union of the suffix box of its first block,
+// the prefix box of its last block and the whole blocks between.  A node's
+// surviving-node count is 2 L - 1 for the L leaves in its range, read from a
+// prefix sum of leaf marks (every surviving internal node has two surviving
+// children).
+//
+// Statistics (deepest node, leaf areas) are reduced per workgroup and summed by
+// one last workgroup: atomics on one address from every wavefront took 13 ns
+// each, 400 us of the emission and 100 us of the areas at 1.0M triangles.
 #include <hip/hip_runtime.h>
 #include <cstring>
 #include <rocprim/device/device_radix_sort.hpp>
@@ -45,6 +49,7 @@ __device__ __forceinline__ float wave_max(float v) {
 }
 
 constexpr int kFitBlock = 256;   // triangles per fitting block (= workgroup size of the block passes)
+constexpr int kFitLevels = 9;    // 2^8 = kFitBlock
 
 // fetch vertices, replace bad triangles by a degenerate one; centroid bounds
 // of the workgroup's triangles to part[6 * blockIdx.x] (min xyz, max xyz)
@@ -273,19 +278,26 @@ struct Tree {
     int32_t* right;
     int32_t* first;    // [nt-1] sorted-primitive range
     int32_t* last;
-    int32_t* flag;     // [nt-1]
     int32_t* axis;     // [nt-1] the axis the node's Morton split separates its children on
     int32_t* cnt;      // [2nt-1] surviving nodes in the subtree
     float4* box;       // [2*(2nt-1)]
     // block fitting (blocks of kFitBlock sorted triangles)
     int32_t* mark;     // [nt] 1 at the first triangle of every leaf
     int32_t* mark_pre; // [nt] exclusive prefix of mark within the block
-    int32_t* blk_base; // [nb+1] leaf marks before each block
     float4* pre;       // [2nt] box of the block's triangles up to k (inclusive)
     float4* suf;       // [2nt] box of the block's triangles from k to the block end
-    float4* st;        // [levels][nb][2] sparse table of block boxes
+    // super-blocks of kFitBlock blocks
+    int32_t* blk_mark; // [nb] leaf marks of each block
+    int32_t* blk_base; // [nb] leaf marks before each block within its super-block
+    float4* blk_pre;   // [2nb] box of the super-block's blocks up to b (inclusive)
+    float4* blk_suf;   // [2nb] box of the super-block's blocks from b on
+    float4* st;        // [kFitLevels][nb][2] box of blocks [b, b + 2^j) within the super-block
+    // the whole mesh
+    int32_t* sup_mark; // [ns] leaf marks of each super-block
+    int32_t* sup_base; // [ns + 1] leaf marks before each super-block, then all
+    float4* sup_st;    // [sup_levels][ns][2] sparse table of super-block boxes
     const int32_t* nbig;   // the big triangles' count (sorted first)
-    int nb, levels;
+    int nb, ns, sup_levels;
 };
 
 // Most triangles a leaf holds: kLeafMax, and kBigLeafMax inside the big
@@ -303,14 +315,17 @@ __device__ __forceinline__ int prefix_len(const uint64_t* keys, int nt, int a, i
     return __clzll((long long)(ka ^ kb));
 }
 
-__global__ void fill_i32(int32_t* p, int64_t n, int32_t v) {
-    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k < n) p[k] = v;
-}
-
-__global__ __launch_bounds__(256) void radix_tree(const uint64_t* keys, int nt, Tree T) {
+__global__ __launch_bounds__(256) void radix_tree(const uint64_t* keys, int nt, Tree T, int32_t* gflag) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= nt - 1) return;
+    // cleared for the passes that set some of their entries
+    T.mark[i] = 0;
+    gflag[i] = 0;
+    gflag[nt - 1 + i] = 0;
+    if (i == 0) {
+        T.mark[nt - 1] = 0;
+        gflag[2 * nt - 2] = 0;
+    }
     const int d = prefix_len(keys, nt, i, i + 1) > prefix_len(keys, nt, i, i - 1) ? 1 : -1;
     const int dmin = prefix_len(keys, nt, i, i - d);
     int lmax = 2;
@@ -342,7 +357,6 @@ __global__ __launch_bounds__(256) void radix_tree(const uint64_t* keys, int nt, 
     T.axis[i] = dnode == 0 ? 3 : dnode < 64 ? 2 - (63 - dnode) % 3 : 0;
     T.parent[L] = i;
     T.parent[R] = i;
-    T.flag[i] = 0;
     if (i == 0) T.parent[0] = -1;
 }
 
@@ -353,14 +367,12 @@ __device__ __forceinline__ void tri_box(const float4* t, float4& lo, float4& hi)
                      fmaxf(t[0].z, fmaxf(t[1].z, t[2].z)), 0.0f);
 }
 
-// fit node p from its two finished children
-__device__ __forceinline__ void fit_node(int p, int nt, const Tree& T) {
-    const int l = T.left[p], r = T.right[p];
-    const float4 al = T.box[2 * l], ah = T.box[2 * l + 1], bl = T.box[2 * r], bh = T.box[2 * r + 1];
-    T.box[2 * p] = make_float4(fminf(al.x, bl.x), fminf(al.y, bl.y), fminf(al.z, bl.z), 0.0f);
-    T.box[2 * p + 1] = make_float4(fmaxf(ah.x, bh.x), fmaxf(ah.y, bh.y), fmaxf(ah.z, bh.z), 0.0f);
-    const int size = T.last[p] - T.first[p] + 1;
-    T.cnt[p] = size <= leaf_cap(T, nt, T.last[p]) ? 1 : 1 + T.cnt[l] + T.cnt[r];
+// rows (v0, v1, v2, 0) of x, y and z from vertices, or vertices from rows
+__device__ __forceinline__ void transpose_tri(const float4* t, float4* out) {
+    const float4 a = t[0], b = t[1], c = t[2];
+    out[0] = make_float4(a.x, b.x, c.x, 0.0f);
+    out[1] = make_float4(a.y, b.y, c.y, 0.0f);
+    out[2] = make_float4(a.z, b.z, c.z, 0.0f);
 }
 
 // leaf marks: a node of <= leaf_cap triangles whose parent has more is a
@@ -380,16 +392,69 @@ __global__ __launch_bounds__(256) void mark_leaves(int nt, Tree T) {
     if (first >= 0 && first < nt) T.mark[first] = 1;
 }
 
-// Block pass (workgroup b = sorted triangles [256 b, 256 b + 256)): leaf
-// boxes, the block's prefix and suffix boxes and leaf-mark prefix, its box
-// (sparse-table level 0) and mark count; then the bottom-up fit of every node
-// inside the block, the second of the two children to arrive fitting the
-// parent.  That climb stays inside one workgroup, so workgroup-scope atomics
-// order it (an agent-scope release would write the L2 back on every step); it
-// stops at the first node spanning blocks.
-__global__ __launch_bounds__(kFitBlock) void fit_block(const float4* tmp, const uint32_t* vals, int nt, Tree T) {
-    __shared__ float4 slo[kFitBlock], shi[kFitBlock];
-    __shared__ int sm[kFitBlock];
+// Boxes of 256 consecutive elements with their sparse table in LDS: level j
+// holds the box of elements [t, t + 2^j) (clamped at the last).
+struct FitTable {
+    float lo[kFitLevels][3][kFitBlock], hi[kFitLevels][3][kFitBlock];
+};
+
+__device__ __forceinline__ void table_put(FitTable& S, int j, int t, float4 lo, float4 hi) {
+    S.lo[j][0][t] = lo.x; S.lo[j][1][t] = lo.y; S.lo[j][2][t] = lo.z;
+    S.hi[j][0][t] = hi.x; S.hi[j][1][t] = hi.y; S.hi[j][2][t] = hi.z;
+}
+
+// levels 1.. from level 0 (thread t its own column; ends with a barrier)
+__device__ void table_build(FitTable& S, int t) {
+    __syncthreads();
+    for (int j = 1; j < kFitLevels; ++j) {
+        const int u = min(t + (1 << (j - 1)), kFitBlock - 1);
+        for (int a = 0; a < 3; ++a) {
+            S.lo[j][a][t] = fminf(S.lo[j - 1][a][t], S.lo[j - 1][a][u]);
+            S.hi[j][a][t] = fmaxf(S.hi[j - 1][a][t], S.hi[j - 1][a][u]);
+        }
+        __syncthreads();
+    }
+}
+
+// box of elements [f, l], 0 <= f <= l < kFitBlock
+__device__ __forceinline__ void table_range(const FitTable& S, int f, int l, float4& lo, float4& hi) {
+    const int j = 31 - __clz(l - f + 1), u = l + 1 - (1 << j);
+    lo = make_float4(fminf(S.lo[j][0][f], S.lo[j][0][u]), fminf(S.lo[j][1][f], S.lo[j][1][u]),
+                     fminf(S.lo[j][2][f], S.lo[j][2][u]), 0.0f);
+    hi = make_float4(fmaxf(S.hi[j][0][f], S.hi[j][0][u]), fmaxf(S.hi[j][1][f], S.hi[j][1][u]),
+                     fmaxf(S.hi[j][2][f], S.hi[j][2][u]), 0.0f);
+}
+
+// exclusive prefix over the workgroup's kFitBlock threads; *total the sum
+__device__ int block_prefix(int v, int* s_wave, int* total) {
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    int incl = v;
+    for (int o = 1; o < 64; o <<= 1) {
+        const int u = __shfl_up(incl, o);
+        incl += lane >= o ? u : 0;
+    }
+    if (lane == 63) s_wave[w] = incl;
+    __syncthreads();
+    int before = 0, sum = 0;
+    for (int k = 0; k < kFitBlock / 64; ++k) {
+        before += k < w ? s_wave[k] : 0;
+        sum += s_wave[k];
+    }
+    *total = sum;
+    return before + incl - v;
+}
+
+// Block pass (workgroup b = sorted triangles [256 b, 256 b + 256)): the
+// triangles' rows in sorted order, leaf boxes, the block's prefix and suffix
+// boxes and leaf-mark prefix, and box and surviving-node count of every node
+// inside the block (node i is one end of its range, so it belongs to block
+// i / 256).  (Fitting bottom-up inside the block instead, the second child to
+// arrive taking the parent, and two more scans took 52 us at 296k triangles
+// and 21 us at 590, now 20 and 8.)
+__global__ __launch_bounds__(kFitBlock) void fit_block(const float4* tmp, const uint32_t* vals, int nt, Tree T,
+                                                       float4* tris_out) {
+    __shared__ FitTable S;
+    __shared__ int s_pre[kFitBlock], s_wave[kFitBlock / 64];
     const int t = threadIdx.x;
     const int lo = blockIdx.x * kFitBlock;
     const int hi = min(nt, lo + kFitBlock) - 1;
@@ -398,102 +463,115 @@ __global__ __launch_bounds__(kFitBlock) void fit_block(const float4* tmp, const 
     float4 blo = make_float4(INFINITY, INFINITY, INFINITY, 0.0f), bhi = make_float4(-INFINITY, -INFINITY, -INFINITY, 0.0f);
     int m = 0;
     if (valid) {
-        tri_box(tmp + 3 * (size_t)vals[k], blo, bhi);
+        const float4* tri = tmp + 3 * (size_t)vals[k];
+        tri_box(tri, blo, bhi);
+        transpose_tri(tri, tris_out + 3 * (size_t)k);
         const int leaf = nt - 1 + k;
         T.box[2 * leaf] = blo;
         T.box[2 * leaf + 1] = bhi;
         T.cnt[leaf] = 1;
         m = T.mark[k];
     }
-    // inclusive prefix (Hillis-Steele) of boxes and marks
-    slo[t] = blo; shi[t] = bhi; sm[t] = m;
+    table_put(S, 0, t, blo, bhi);
+    table_build(S, t);
+    int total = 0;
+    const int mp = block_prefix(m, s_wave, &total);
+    s_pre[t] = mp;
     __syncthreads();
-    for (int o = 1; o < kFitBlock; o <<= 1) {
-        float4 al = slo[t], ah = shi[t];
-        int am = sm[t];
-        if (t >= o) {
-            const float4 bl = slo[t - o], bh = shi[t - o];
-            al = make_float4(fminf(al.x, bl.x), fminf(al.y, bl.y), fminf(al.z, bl.z), 0.0f);
-            ah = make_float4(fmaxf(ah.x, bh.x), fmaxf(ah.y, bh.y), fmaxf(ah.z, bh.z), 0.0f);
-            am += sm[t - o];
-        }
-        __syncthreads();
-        slo[t] = al; shi[t] = ah; sm[t] = am;
-        __syncthreads();
-    }
+    float4 al, ah;
     if (valid) {
-        T.pre[2 * k] = slo[t];
-        T.pre[2 * k + 1] = shi[t];
-        T.mark_pre[k] = sm[t] - m;
-    }
-    if (k == hi) {
-        T.st[2 * blockIdx.x] = slo[t];
-        T.st[2 * blockIdx.x + 1] = shi[t];
-        T.blk_base[blockIdx.x] = sm[t];   // the block's mark count (scanned by block_table)
-    }
-    __syncthreads();
-    // suffix: the same scan from the block end
-    slo[t] = blo; shi[t] = bhi;
-    __syncthreads();
-    for (int o = 1; o < kFitBlock; o <<= 1) {
-        float4 al = slo[t], ah = shi[t];
-        if (t + o < kFitBlock) {
-            const float4 bl = slo[t + o], bh = shi[t + o];
-            al = make_float4(fminf(al.x, bl.x), fminf(al.y, bl.y), fminf(al.z, bl.z), 0.0f);
-            ah = make_float4(fmaxf(ah.x, bh.x), fmaxf(ah.y, bh.y), fmaxf(ah.z, bh.z), 0.0f);
+        table_range(S, 0, t, al, ah);
+        T.pre[2 * (size_t)k] = al;
+        T.pre[2 * (size_t)k + 1] = ah;
+        T.mark_pre[k] = mp;
+        if (k == hi) {
+            T.st[2 * (size_t)blockIdx.x] = al;
+            T.st[2 * (size_t)blockIdx.x + 1] = ah;
+            T.blk_mark[blockIdx.x] = total;
         }
-        __syncthreads();
-        slo[t] = al; shi[t] = ah;
-        __syncthreads();
+        table_range(S, t, kFitBlock - 1, al, ah);   // (past the last triangle: empty boxes)
+        T.suf[2 * (size_t)k] = al;
+        T.suf[2 * (size_t)k + 1] = ah;
     }
-    if (valid) {
-        T.suf[2 * k] = slo[t];
-        T.suf[2 * k + 1] = shi[t];
-    }
-    if (!valid) return;
-    int p = T.parent[nt - 1 + k];
-    for (int guard = 0; p >= 0 && p < nt - 1 && guard < 4096; ++guard) {
-        if (T.first[p] < lo || T.last[p] > hi) return;   // spans blocks: fit_top
-        const int old = __hip_atomic_fetch_add(&T.flag[p], 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_WORKGROUP);
-        if (old == 0) return;
-        fit_node(p, nt, T);
-        p = T.parent[p];
+    if (k < nt - 1) {
+        const int f = T.first[k], l = T.last[k];
+        if (f >= lo && l <= hi && f < l) {
+            table_range(S, f - lo, l - lo, al, ah);
+            T.box[2 * (size_t)k] = al;
+            T.box[2 * (size_t)k + 1] = ah;
+            const int leaves = (l < hi ? s_pre[l + 1 - lo] : total) - s_pre[f - lo];
+            T.cnt[k] = l - f + 1 <= leaf_cap(T, nt, l) ? 1 : 2 * leaves - 1;
+        }
     }
 }
 
-// One workgroup: exclusive scan of the block mark counts (blk_base, with the
-// total at nb) and the sparse table over block boxes, level j holding the box
-// of blocks [b, b + 2^j) (clamped at the last block).
-__global__ __launch_bounds__(1024) void block_table(Tree T) {
-    __shared__ int s[1024];
-    const int t = threadIdx.x, nb = T.nb;
-    int carry = 0;
-    for (int c0 = 0; c0 < nb; c0 += 1024) {
-        const int b = c0 + t;
-        const int v = b < nb ? T.blk_base[b] : 0;
-        s[t] = v;
-        __syncthreads();
-        for (int o = 1; o < 1024; o <<= 1) {
-            const int a = t >= o ? s[t - o] : 0;
-            __syncthreads();
-            s[t] += a;
-            __syncthreads();
-        }
-        if (b < nb) T.blk_base[b] = carry + s[t] - v;
-        const int tot = s[1023];
-        __syncthreads();
-        carry += tot;
+// The same over the boxes of a super-block's blocks.
+__global__ __launch_bounds__(kFitBlock) void fit_super(Tree T) {
+    __shared__ FitTable S;
+    __shared__ int s_wave[kFitBlock / 64];
+    const int t = threadIdx.x;
+    const int b = blockIdx.x * kFitBlock + t;
+    const int last = min(T.nb, (int)(blockIdx.x + 1) * kFitBlock) - 1;
+    const bool valid = b <= last;
+    float4 lo = make_float4(INFINITY, INFINITY, INFINITY, 0.0f), hi = make_float4(-INFINITY, -INFINITY, -INFINITY, 0.0f);
+    int m = 0;
+    if (valid) {
+        lo = T.st[2 * (size_t)b];
+        hi = T.st[2 * (size_t)b + 1];
+        m = T.blk_mark[b];
     }
-    if (t == 0) T.blk_base[nb] = carry;
-    for (int j = 1; j < T.levels; ++j) {
-        const float4* prev = T.st + 2 * (size_t)(j - 1) * nb;
-        float4* cur = T.st + 2 * (size_t)j * nb;
-        const int h = 1 << (j - 1);
-        for (int b = t; b < nb; b += 1024) {
-            const int b2 = min(b + h, nb - 1);
-            const float4 al = prev[2 * b], ah = prev[2 * b + 1], bl = prev[2 * b2], bh = prev[2 * b2 + 1];
-            cur[2 * b] = make_float4(fminf(al.x, bl.x), fminf(al.y, bl.y), fminf(al.z, bl.z), 0.0f);
-            cur[2 * b + 1] = make_float4(fmaxf(ah.x, bh.x), fmaxf(ah.y, bh.y), fmaxf(ah.z, bh.z), 0.0f);
+    table_put(S, 0, t, lo, hi);
+    table_build(S, t);
+    int total = 0;
+    const int mp = block_prefix(m, s_wave, &total);
+    if (!valid) return;
+    T.blk_base[b] = mp;
+    for (int j = 1; j < kFitLevels; ++j) {
+        float4* st = T.st + 2 * ((size_t)j * T.nb + b);
+        st[0] = make_float4(S.lo[j][0][t], S.lo[j][1][t], S.lo[j][2][t], 0.0f);
+        st[1] = make_float4(S.hi[j][0][t], S.hi[j][1][t], S.hi[j][2][t], 0.0f);
+    }
+    table_range(S, 0, t, lo, hi);
+    T.blk_pre[2 * (size_t)b] = lo;
+    T.blk_pre[2 * (size_t)b + 1] = hi;
+    if (b == last) {
+        T.sup_st[2 * (size_t)blockIdx.x] = lo;
+        T.sup_st[2 * (size_t)blockIdx.x + 1] = hi;
+        T.sup_mark[blockIdx.x] = total;
+        if (T.ns == 1) {
+            T.sup_base[0] = 0;
+            T.sup_base[1] = total;
+        }
+    }
+    table_range(S, t, kFitBlock - 1, lo, hi);
+    T.blk_suf[2 * (size_t)b] = lo;
+    T.blk_suf[2 * (size_t)b + 1] = hi;
+}
+
+// Over the super-blocks (one workgroup; at most 1024 of them, 2^26 triangles):
+// scan of their leaf marks and the sparse table of their boxes.
+__global__ __launch_bounds__(1024) void fit_mesh(Tree T) {
+    __shared__ int s[1024];
+    const int t = threadIdx.x, ns = T.ns;
+    const int v = t < ns ? T.sup_mark[t] : 0;
+    s[t] = v;
+    __syncthreads();
+    for (int o = 1; o < 1024; o <<= 1) {
+        const int a = t >= o ? s[t - o] : 0;
+        __syncthreads();
+        s[t] += a;
+        __syncthreads();
+    }
+    if (t < ns) T.sup_base[t] = s[t] - v;
+    if (t == 0) T.sup_base[ns] = s[1023];
+    for (int j = 1; j < T.sup_levels; ++j) {
+        const float4* prev = T.sup_st + 2 * (size_t)(j - 1) * ns;
+        float4* cur = T.sup_st + 2 * (size_t)j * ns;
+        if (t < ns) {
+            const int u = min(t + (1 << (j - 1)), ns - 1);
+            const float4 al = prev[2 * t], ah = prev[2 * t + 1], bl = prev[2 * u], bh = prev[2 * u + 1];
+            cur[2 * t] = make_float4(fminf(al.x, bl.x), fminf(al.y, bl.y), fminf(al.z, bl.z), 0.0f);
+            cur[2 * t + 1] = make_float4(fmaxf(ah.x, bh.x), fmaxf(ah.y, bh.y), fmaxf(ah.z, bh.z), 0.0f);
         }
         __syncthreads();
     }
@@ -506,7 +584,9 @@ __device__ __forceinline__ void grow(float4& lo, float4& hi, const float4* b) {
 
 // leaves before sorted position i (i in [0, nt])
 __device__ __forceinline__ int leaves_before(const Tree& T, int nt, int i) {
-    return i >= nt ? T.blk_base[T.nb] : T.blk_base[i / kFitBlock] + T.mark_pre[i];
+    if (i >= nt) return T.sup_base[T.ns];
+    const int b = i / kFitBlock;
+    return T.sup_base[b / kFitBlock] + T.blk_base[b] + T.mark_pre[i];
 }
 
 // every internal node spanning blocks: box and surviving-node count directly
@@ -517,17 +597,28 @@ __global__ __launch_bounds__(256) void fit_top(int nt, Tree T) {
     if (f < 0 || l >= nt || f > l) return;
     const int bf = f / kFitBlock, bl = l / kFitBlock;
     if (bf == bl) return;   // fitted by its block
-    float4 lo = T.suf[2 * f], hi = T.suf[2 * f + 1];
+    float4 lo = T.suf[2 * (size_t)f], hi = T.suf[2 * (size_t)f + 1];
     grow(lo, hi, T.pre + 2 * (size_t)l);
-    const int n = bl - bf - 1;   // whole blocks strictly between
-    if (n > 0) {
-        int j = 31 - __clz(n);
-        j = min(j, T.levels - 1);
-        grow(lo, hi, T.st + 2 * ((size_t)j * T.nb + bf + 1));
-        grow(lo, hi, T.st + 2 * ((size_t)j * T.nb + (bl - (1 << j))));
+    const int b0 = bf + 1, b1 = bl - 1;   // whole blocks strictly between
+    if (b0 <= b1) {
+        const int s0 = b0 / kFitBlock, s1 = b1 / kFitBlock;
+        if (s0 == s1) {
+            const int j = 31 - __clz(b1 - b0 + 1);
+            grow(lo, hi, T.st + 2 * ((size_t)j * T.nb + b0));
+            grow(lo, hi, T.st + 2 * ((size_t)j * T.nb + (b1 + 1 - (1 << j))));
+        } else {
+            grow(lo, hi, T.blk_suf + 2 * (size_t)b0);
+            grow(lo, hi, T.blk_pre + 2 * (size_t)b1);
+            const int n = s1 - s0 - 1;    // whole super-blocks between
+            if (n > 0) {
+                const int j = 31 - __clz(n);
+                grow(lo, hi, T.sup_st + 2 * ((size_t)j * T.ns + s0 + 1));
+                grow(lo, hi, T.sup_st + 2 * ((size_t)j * T.ns + (s1 - (1 << j))));
+            }
+        }
     }
-    T.box[2 * p] = lo;
-    T.box[2 * p + 1] = hi;
+    T.box[2 * (size_t)p] = lo;
+    T.box[2 * (size_t)p + 1] = hi;
     T.cnt[p] = 2 * (leaves_before(T, nt, l + 1) - leaves_before(T, nt, f)) - 1;
 }
 
@@ -585,10 +676,22 @@ __device__ QNode quantise(const QFrame& F, const Node& nd) {
     return q;
 }
 
-__global__ __launch_bounds__(256) void emit(int nt, Tree T, Node* out, QNode* qout, QFrame* frame,
-                                            DeviceSceneInfo* info, int32_t* gflag, int32_t* naxis) {
-    const int x = blockIdx.x * blockDim.x + threadIdx.x;
-    if (x >= 2 * nt - 1) return;
+__device__ __forceinline__ double box_area(const Node& nd) {
+    const double dx = fmax((double)nd.hi[0] - nd.lo[0], 0.0), dy = fmax((double)nd.hi[1] - nd.lo[1], 0.0),
+                 dz = fmax((double)nd.hi[2] - nd.lo[2], 0.0);
+    return 2.0 * (dx * dy + dy * dz + dz * dx);
+}
+
+// a workgroup's share of the statistics
+struct EmitPart {
+    double leaf_area;
+    int32_t max_depth;
+};
+
+// one surviving node x at its pre-order index, with its depth and, of a leaf,
+// its box's area
+__device__ __forceinline__ void emit_node(int x, int nt, const Tree& T, Node* out, QNode* qout, QFrame* frame,
+                                          int32_t* gflag, int32_t* naxis, int& max_depth, double& area) {
     const bool is_prim = x >= nt - 1;
     if (x != 0) {
         const int p = T.parent[x];
@@ -627,21 +730,30 @@ __global__ __launch_bounds__(256) void emit(int nt, Tree T, Node* out, QNode* qo
     if (idx == 0) *frame = F;
     // a wide node for the root and for every internal node at even depth
     gflag[idx] = (idx == 0 || (payload == 0 && (depth & 1) == 0)) ? 1 : 0;
-    atomicMax(&info->max_depth, depth);
-    if (x == 0) info->n_nodes = T.cnt[0];
+    if (payload != 0) area = box_area(nd);
+    max_depth = depth;
 }
 
-// rows (v0, v1, v2, 0) of x, y and z from vertices, or vertices from rows
-__device__ __forceinline__ void transpose_tri(const float4* t, float4* out) {
-    const float4 a = t[0], b = t[1], c = t[2];
-    out[0] = make_float4(a.x, b.x, c.x, 0.0f);
-    out[1] = make_float4(a.y, b.y, c.y, 0.0f);
-    out[2] = make_float4(a.z, b.z, c.z, 0.0f);
-}
-
-__global__ void reorder(const float4* tmp, const uint32_t* vals, int64_t nt, float4* out) {
-    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k < nt) transpose_tri(tmp + 3 * (size_t)vals[k], out + 3 * k);
+__global__ __launch_bounds__(256) void emit(int nt, Tree T, Node* out, QNode* qout, QFrame* frame,
+                                            int32_t* gflag, int32_t* naxis, EmitPart* part) {
+    const int x = blockIdx.x * blockDim.x + threadIdx.x;
+    int depth = -1;
+    double area = 0.0;
+    if (x < 2 * nt - 1) emit_node(x, nt, T, out, qout, frame, gflag, naxis, depth, area);
+    __shared__ int s_depth[4];
+    __shared__ double s_area[4];
+    for (int o = 32; o > 0; o >>= 1) {
+        depth = max(depth, __shfl_xor(depth, o));
+        area += __shfl_xor(area, o);
+    }
+    if ((threadIdx.x & 63) == 0) {
+        s_depth[threadIdx.x >> 6] = depth;
+        s_area[threadIdx.x >> 6] = area;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0)
+        part[blockIdx.x] = EmitPart{s_area[0] + s_area[1] + s_area[2] + s_area[3],
+                                    max(max(s_depth[0], s_depth[1]), max(s_depth[2], s_depth[3]))};
 }
 
 __global__ __launch_bounds__(256) void tri_vertices(const float4* rows, int64_t n, float4* verts) {
@@ -803,10 +915,6 @@ __global__ void tiny_scene(const float4* tmp, int nt, Node* out, float4* tris_ou
     info->n_groups = 1;
 }
 
-__global__ void count_groups(const int32_t* gflag, const int32_t* gidx, int n, DeviceSceneInfo* info) {
-    info->n_groups = gidx[n - 1] + gflag[n - 1];
-}
-
 __global__ void init_info(DeviceSceneInfo* info) {
     info->n_nodes = 0;
     info->max_depth = 0;
@@ -816,33 +924,39 @@ __global__ void init_info(DeviceSceneInfo* info) {
     info->wide_bad = 0;
     info->n_big = 0;
     info->depth_complexity = 0.0f;
-    info->leaf_area = 0.0;
 }
 
-__device__ __forceinline__ double box_area(const Node& nd) {
-    const double dx = fmax((double)nd.hi[0] - nd.lo[0], 0.0), dy = fmax((double)nd.hi[1] - nd.lo[1], 0.0),
-                 dz = fmax((double)nd.hi[2] - nd.lo[2], 0.0);
-    return 2.0 * (dx * dy + dy * dz + dz * dx);
-}
-
-// the leaf boxes' surface areas, summed into info->leaf_area
-__global__ __launch_bounds__(256) void leaf_area_sum(const Node* out, int n_max, DeviceSceneInfo* info) {
-    __shared__ double part[4];
-    const int x = blockIdx.x * blockDim.x + threadIdx.x;
+// Node counts, depth, and the depth complexity with the class it selects (one
+// workgroup; the areas are summed in a fixed order).
+__global__ __launch_bounds__(256) void finish_info(const Node* out, const EmitPart* part, int n_part, const int32_t* gflag,
+                                                   const int32_t* gidx, int n_max, DeviceSceneInfo* info) {
+    __shared__ double s_area[256];
+    __shared__ int s_depth[256];
+    const int t = threadIdx.x;
     double a = 0.0;
-    if (x < n_max && x < out[0].escape && out[x].payload != 0) a = box_area(out[x]);
-    for (int o = 32; o > 0; o >>= 1) a += __shfl_xor(a, o);
-    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = a;
+    int d = 0;
+    for (int k = t; k < n_part; k += 256) {
+        a += part[k].leaf_area;
+        d = max(d, part[k].max_depth);
+    }
+    s_area[t] = a;
+    s_depth[t] = d;
     __syncthreads();
-    if (threadIdx.x == 0) atomicAdd(&info->leaf_area, part[0] + part[1] + part[2] + part[3]);
-}
-
-// depth complexity and the traversal it selects
-__global__ void choose_walk(const Node* out, DeviceSceneInfo* info) {
+    for (int o = 128; o > 0; o >>= 1) {
+        if (t < o) {
+            s_area[t] += s_area[t + o];
+            s_depth[t] = max(s_depth[t], s_depth[t + o]);
+        }
+        __syncthreads();
+    }
+    if (t != 0) return;
     const double root = box_area(out[0]);
-    const double d = root > 0.0 ? info->leaf_area / root : 0.0;
-    info->depth_complexity = (float)d;
-    info->wide = (d >= (double)kWideDepthComplexity && info->wide_bad == 0) ? 1 : 0;
+    const double c = root > 0.0 ? s_area[0] / root : 0.0;
+    info->n_nodes = out[0].escape;
+    info->max_depth = s_depth[0];
+    info->n_groups = gidx[n_max - 1] + gflag[n_max - 1];
+    info->depth_complexity = (float)c;
+    info->wide = (c >= (double)kWideDepthComplexity && info->wide_bad == 0) ? 1 : 0;
 }
 
 inline unsigned nblk(int64_t n) { return (unsigned)((n + 255) / 256); }
@@ -877,17 +991,21 @@ hipError_t build_bvh(const float* verts, int64_t nv, const int32_t* tris, int64_
     auto al = [](size_t b) { return (b + 255) & ~(size_t)255; };
     const size_t ntm = nt > 0 ? (size_t)nt : 1;
     const int nb = (int)((ntm + kFitBlock - 1) / kFitBlock);
-    int levels = 1;
-    while ((1 << levels) <= nb) ++levels;   // 2^(levels-1) <= nb < 2^levels
+    const int ns = (nb + kFitBlock - 1) / kFitBlock;   // super-blocks
+    int sup_levels = 1;
+    while ((1 << sup_levels) <= ns) ++sup_levels;      // 2^(sup_levels-1) <= ns < 2^sup_levels
+    const unsigned n_part = nblk((int64_t)n_nodes);
     const size_t sz_tmp = al(sizeof(float4) * 3 * ntm), sz_keys = al(sizeof(uint64_t) * ntm),
                  sz_vals = al(sizeof(uint32_t) * ntm), sz_i = al(sizeof(int32_t) * n_nodes),
                  sz_box = al(sizeof(float4) * 2 * n_nodes), sz_cb = al(sizeof(int) * 8), sz_sort = al(sort_bytes),
                  sz_part = al(sizeof(float) * 6 * (size_t)nblk(ntm)), sz_nt = al(sizeof(int32_t) * ntm),
-                 sz_base = al(sizeof(int32_t) * (size_t)(nb + 1)), sz_pre = al(sizeof(float4) * 2 * ntm),
-                 sz_st = al(sizeof(float4) * 2 * (size_t)nb * (size_t)levels);
+                 sz_nb = al(sizeof(int32_t) * (size_t)nb), sz_pre = al(sizeof(float4) * 2 * ntm),
+                 sz_bpre = al(sizeof(float4) * 2 * (size_t)nb), sz_st = al(sizeof(float4) * 2 * (size_t)nb * kFitLevels),
+                 sz_ns = al(sizeof(int32_t) * (size_t)(ns + 1)),
+                 sz_sst = al(sizeof(float4) * 2 * (size_t)ns * (size_t)sup_levels), sz_ep = al(sizeof(EmitPart) * n_part);
     const size_t sz_scan = al(scan_bytes);
-    const size_t total = sz_tmp + 2 * sz_keys + 2 * sz_vals + 11 * sz_i + sz_box + sz_cb + sz_sort + sz_part +
-                         2 * sz_nt + sz_base + 2 * sz_pre + sz_st + sz_scan;
+    const size_t total = sz_tmp + 2 * sz_keys + 2 * sz_vals + 10 * sz_i + sz_box + sz_cb + sz_sort + sz_part + 2 * sz_nt +
+                         2 * sz_nb + 2 * sz_pre + 2 * sz_bpre + sz_st + 2 * sz_ns + sz_sst + sz_ep + sz_scan;
     char* base = (char*)ta.alloc(ta.ctx, total, s);
     if (!base) { *oom = 1; return hipErrorOutOfMemory; }
     char* p = base;
@@ -903,7 +1021,6 @@ hipError_t build_bvh(const float* verts, int64_t nv, const int32_t* tris, int64_
     T.right = (int32_t*)take(sz_i);
     T.first = (int32_t*)take(sz_i);
     T.last = (int32_t*)take(sz_i);
-    T.flag = (int32_t*)take(sz_i);
     T.axis = (int32_t*)take(sz_i);
     T.cnt = (int32_t*)take(sz_i);
     T.box = (float4*)take(sz_box);
@@ -912,10 +1029,17 @@ hipError_t build_bvh(const float* verts, int64_t nv, const int32_t* tris, int64_
     float* part = (float*)take(sz_part);
     T.mark = (int32_t*)take(sz_nt);
     T.mark_pre = (int32_t*)take(sz_nt);
-    T.blk_base = (int32_t*)take(sz_base);
     T.pre = (float4*)take(sz_pre);
     T.suf = (float4*)take(sz_pre);
+    T.blk_mark = (int32_t*)take(sz_nb);
+    T.blk_base = (int32_t*)take(sz_nb);
+    T.blk_pre = (float4*)take(sz_bpre);
+    T.blk_suf = (float4*)take(sz_bpre);
     T.st = (float4*)take(sz_st);
+    T.sup_mark = (int32_t*)take(sz_ns);
+    T.sup_base = (int32_t*)take(sz_ns);
+    T.sup_st = (float4*)take(sz_sst);
+    EmitPart* eparts = (EmitPart*)take(sz_ep);
     int32_t* gflag = (int32_t*)take(sz_i);
     int32_t* gidx = (int32_t*)take(sz_i);
     int32_t* naxis = (int32_t*)take(sz_i);
@@ -923,7 +1047,8 @@ hipError_t build_bvh(const float* verts, int64_t nv, const int32_t* tris, int64_
     // the hoisted nodes follow the wide nodes in the same allocation
     QNode* top = groups_out + 4 * ntm;
     T.nb = nb;
-    T.levels = levels;
+    T.ns = ns;
+    T.sup_levels = sup_levels;
     T.nbig = &info->n_big;
     hipError_t err = hipSuccess;
     if (nt > 0) {
@@ -938,18 +1063,14 @@ hipError_t build_bvh(const float* verts, int64_t nv, const int32_t* tris, int64_
         err = rocprim::radix_sort_pairs(sort_tmp, sort_bytes, keys, keys2, vals, vals2, (size_t)nt, 0, 64, s);
         if (err == hipSuccess) {
             hipLaunchKernelGGL(big_sah, dim3(1), dim3(3 * kBigSah), 0, s, tmp, nt, keys2, vals2, info);
-            hipLaunchKernelGGL(fill_i32, dim3(nblk(2 * nt - 1)), dim3(256), 0, s, T.parent, (int64_t)(2 * nt - 1), -1);
-            hipLaunchKernelGGL(fill_i32, dim3(nblk(2 * nt - 1)), dim3(256), 0, s, T.cnt, (int64_t)(2 * nt - 1), 0);
-            hipLaunchKernelGGL(fill_i32, dim3(nblk(nt)), dim3(256), 0, s, T.mark, (int64_t)nt, 0);
-            hipLaunchKernelGGL(radix_tree, dim3(nblk(nt - 1)), dim3(256), 0, s, keys2, nt, T);
+            hipLaunchKernelGGL(radix_tree, dim3(nblk(nt - 1)), dim3(256), 0, s, keys2, nt, T, gflag);
             hipLaunchKernelGGL(mark_leaves, dim3(nblk(2 * nt - 1)), dim3(256), 0, s, nt, T);
-            hipLaunchKernelGGL(fit_block, dim3((unsigned)nb), dim3(kFitBlock), 0, s, tmp, vals2, nt, T);
-            hipLaunchKernelGGL(block_table, dim3(1), dim3(1024), 0, s, T);
-            hipLaunchKernelGGL(fit_top, dim3(nblk(nt - 1)), dim3(256), 0, s, nt, T);
-            hipLaunchKernelGGL(fill_i32, dim3(nblk(2 * nt - 1)), dim3(256), 0, s, gflag, (int64_t)(2 * nt - 1), 0);
-            hipLaunchKernelGGL(emit, dim3(nblk(2 * nt - 1)), dim3(256), 0, s, nt, T, nodes_out, qnodes_out,
-                               frame_out, info, gflag, naxis);
-            hipLaunchKernelGGL(reorder, dim3(nblk(nt)), dim3(256), 0, s, tmp, vals2, (int64_t)nt, tris_out);
+            hipLaunchKernelGGL(fit_block, dim3((unsigned)nb), dim3(kFitBlock), 0, s, tmp, vals2, nt, T, tris_out);
+            hipLaunchKernelGGL(fit_super, dim3((unsigned)ns), dim3(kFitBlock), 0, s, T);
+            if (ns > 1) hipLaunchKernelGGL(fit_mesh, dim3(1), dim3(1024), 0, s, T);
+            if (nb > 1) hipLaunchKernelGGL(fit_top, dim3(nblk(nt - 1)), dim3(256), 0, s, nt, T);
+            hipLaunchKernelGGL(emit, dim3(n_part), dim3(256), 0, s, nt, T, nodes_out, qnodes_out, frame_out, gflag, naxis,
+                               eparts);
             err = rocprim::exclusive_scan(scan_tmp, scan_bytes, gflag, gidx, 0, (size_t)(2 * nt - 1),
                                           rocprim::plus<int32_t>(), s);
         }
@@ -957,9 +1078,8 @@ hipError_t build_bvh(const float* verts, int64_t nv, const int32_t* tris, int64_
             hipLaunchKernelGGL(wide_groups, dim3(nblk(2 * nt - 1)), dim3(256), 0, s, nodes_out, qnodes_out, gflag,
                                gidx, naxis, 2 * nt - 1, groups_out, info);
             hipLaunchKernelGGL(hoist_top, dim3(1), dim3(64), 0, s, groups_out, top);
-            hipLaunchKernelGGL(count_groups, dim3(1), dim3(1), 0, s, gflag, gidx, 2 * nt - 1, info);
-            hipLaunchKernelGGL(leaf_area_sum, dim3(nblk(2 * nt - 1)), dim3(256), 0, s, nodes_out, 2 * nt - 1, info);
-            hipLaunchKernelGGL(choose_walk, dim3(1), dim3(1), 0, s, nodes_out, info);
+            hipLaunchKernelGGL(finish_info, dim3(1), dim3(256), 0, s, nodes_out, eparts, (int)n_part, gflag, gidx,
+                               2 * nt - 1, info);
         }
     }
     if (err == hipSuccess) err = hipGetLastError();

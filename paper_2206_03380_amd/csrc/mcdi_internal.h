@@ -44,7 +44,6 @@ struct DeviceSceneInfo {
     float depth_complexity;    // sum of leaf box areas / root box area
     int32_t wide_bad;          // a wide reference failed the builder's check
     int32_t n_big;             // big triangles (the root's first subtree when 0 < n_big < n_tris)
-    double leaf_area;          // the sum (accumulated by the builder)
 };
 
 // The scene's quantisation frame: node box coordinates as half-precision
