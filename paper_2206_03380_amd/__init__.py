@@ -473,13 +473,13 @@ def bilateral_bwd(guide, g_out, wsum, stream=None, out=None):
 
 def trace_anyhit(scene, orig, dirs, brute=False, stream=None, mode=None):
     """orig, dirs: device f32 [3, n].  Returns uint8 [n] (1 = occluded).
-    mode: "binary", "brute" or "wide" (default: "brute" if brute else
-    "binary")."""
+    mode: "binary", "brute" or "wide", which give the same answer (default:
+    "brute" if brute else "wide", the shading calls' traversal and the fastest)."""
     n = orig.shape[1]
     _need(orig, torch.float32, (3, n), "orig")
     _need(dirs, torch.float32, (3, n), "dirs")
     hit = torch.empty(n, dtype=torch.uint8, device=orig.device)
-    m = {"binary": 0, "brute": 1, "wide": 2}[mode or ("brute" if brute else "binary")]
+    m = {"binary": 0, "brute": 1, "wide": 2}[mode or ("brute" if brute else "wide")]
     L.check(L.lib().mcdi_trace_anyhit(scene.handle, _ptr(orig), _ptr(dirs), n, _ptr(hit), m, _stream(stream)))
     return hit
 

@@ -236,69 +236,6 @@ __global__ __launch_bounds__(kBlock, 8) void edge_gen_kernel(EdgeArgs E) {
     }
 }
 
-// Any-hit query of one ray by a whole wavefront over the 4-wide hierarchy.  The
-// wave keeps one stack of references in LDS: each step takes the top 64 (or
-// all), a lane to each -- a node's hit children go back onto the stack, a
-// leaf's triangles are tested -- so a ray that misses costs about as many
-// dependent steps as the tree has levels, and one that hits stops with the
-// step that finds it.  (One lane per subtree, each walking its own with skip
-// links, took the longest subtree's walk: 3,400 rays against 102k triangles
-// 184 us, now 42.)  A stack that would
-// overflow hands the ray to the binary walk of a lane.  The ray must be
-// the same in every lane; the result is uniform.
-constexpr int kWaveStack = 1024;
-__device__ __forceinline__ bool wave_anyhit(const Scene& sc, const Ray& r, int n_total, uint32_t* stack) {
-    if (n_total <= 0) return false;
-    const uint4* g = reinterpret_cast<const uint4*>(sc.groups);
-    const uint32_t n_groups = sc.group_bytes / 64u;
-    const QRay q = make_qray(r, *sc.frame);
-    const int lane = __lane_id();
-    const uint64_t lt = (1ull << lane) - 1ull;
-    bool flat = sc.info->wide_bad != 0;
-    int n = 1;
-    if (lane == 0) stack[0] = 0u;
-    while (n > 0 && !flat) {
-        const int take = min(n, 64);
-        n -= take;
-        bool hit = false;
-        uint32_t w[4] = {0u, 0u, 0u, 0u};
-        __builtin_amdgcn_wave_barrier();   // the pushes of the last step come first
-        if (lane < take) {
-            const uint32_t ref = stack[n + lane];
-            if (ref & kQLeaf) {
-                uint32_t nt = 0;
-                hit = leaf_anyhit<false>(sc, r, ref, nt);
-            } else if (ref < n_groups) {
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const uint4 c = g[4 * (size_t)ref + k];
-                    w[k] = qbox_hit(q, c) ? c.w : 0u;
-                }
-            }
-        }
-        if (__any(hit)) return true;
-        __builtin_amdgcn_wave_barrier();
-        uint64_t live[4];
-        int total = n;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            live[k] = __ballot(w[k] != 0u);
-            total += (int)__popcll(live[k]);
-        }
-        flat = total > kWaveStack;
-        if (!flat) {
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                if (w[k] != 0u) stack[n + (int)__popcll(live[k] & lt)] = w[k] & kRefMask;
-                n += (int)__popcll(live[k]);
-            }
-        }
-    }
-    if (!flat) return false;
-    uint32_t nb = 0, nt = 0;
-    return qbvh_anyhit(sc, r, q, n_total, nb, nt);
-}
-
 // a queued sample recomputed: ray origin, out-side direction, the term and
 // where it goes (false: the sample carries no term)
 struct EdgeTerm {
@@ -423,7 +360,8 @@ __global__ __launch_bounds__(256) void edge_trace_kernel(EdgeArgs E) {
         EdgeTerm T;
         if (!edge_term(E, E.queue[i], ne, ns, scale, bil, T)) continue;
         ++c_rays;
-        if (wave_anyhit(sc, make_ray(T.o, T.wo), n_total, s_stack[threadIdx.x >> 6])) {
+        const Ray ray = make_ray(T.o, T.wo);
+        if (wave_anyhit<64, kWaveStack>(sc, ray, make_qray(ray, *sc.frame), n_total, s_stack[threadIdx.x >> 6])) {
             ++c_hits;
             continue;
         }

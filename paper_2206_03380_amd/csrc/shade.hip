@@ -377,7 +377,6 @@ __device__ __forceinline__ void gen_tile(const ShadeArgs& A, int64_t tile, float
     const uint32_t vid = (uint32_t)A.g.view_base + view;
     const uint32_t k0 = (uint32_t)A.seed, k1 = (uint32_t)(A.seed >> 32);
     const int lane = __lane_id();
-    const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
     uint32_t c_rays = 0, c_culled = 0;
     uint32_t lw = 0u;   // live bits of the current word
     for (int s = 0; s < spp; ++s) {
@@ -405,7 +404,7 @@ __device__ __forceinline__ void gen_tile(const ShadeArgs& A, int64_t tile, float
             if (want) {
                 const int slot = 2 * s + tech;
                 const uint32_t tag = (uint32_t)threadIdx.x | ((uint32_t)slot << 8);
-                region[base + (int)__popcll(bal & lt)] = make_float4(S.w.x, S.w.y, S.w.z, __uint_as_float(tag));
+                region[base + bits_below(bal)] = make_float4(S.w.x, S.w.y, S.w.z, __uint_as_float(tag));
                 lw |= 1u << (slot & 31);
                 ++c_rays;
             }
@@ -462,13 +461,67 @@ __device__ __forceinline__ void gen_tile(const ShadeArgs& A, int64_t tile, float
 // after a visit's pushes (the visit pops one again), and three spare rows for
 // its last stores.  Eight workgroups per CU fit, with the hoisted nodes.
 constexpr int kStack = 13, kStackRows = 1 + kStack + 4;
+// references a full stack hands to private memory at a time, and how many it
+// holds (a ray that needs more walks the binary nodes from the root)
+constexpr uint32_t kSpill = 8, kSpillMax = 32;
+// stands for them at the bottom of the stack: a leaf reference past every
+// triangle array that no record holds
+constexpr uint32_t kMoreRef = leaf_ref((1u << 26) - 1u, 2u);
+static_assert(kMoreRef != kEmptyRef && kMoreRef != kWideNone && (kMoreRef & kRefMask) == kMoreRef, "");
 
-template <bool COUNT>
-__device__ __forceinline__ void trace_tile(const ShadeArgs& A, int64_t tile, const float4* R, int count,
-                                           uint32_t* hitbits, int* s_next, uint32_t* s_stack, uint4* s_top) {
-    const Scene& sc = A.scene;
-    const int64_t N = A.g.n;
-    const int64_t base_pix = tile * kBlock;
+// a struct of words as lane l holds it
+template <typename T>
+__device__ __forceinline__ T read_lane(const T& v, int l) {
+    struct Words { uint32_t w[sizeof(T) / 4]; };
+    Words u = __builtin_bit_cast(Words, v);
+#pragma unroll
+    for (uint32_t k = 0; k < sizeof(T) / 4; ++k) u.w[k] = (uint32_t)__builtin_amdgcn_readlane((int)u.w[k], l);
+    return __builtin_bit_cast(T, u);
+}
+
+// Where a walk's rays come from and its hits go to: take() gives ray idx and
+// its tag, which hit() gets back.
+struct TileFeed {      // a tile's generated shadow rays, and the hit bits
+    const float4* R;
+    const float4* origins;   // of the tile's first pixel
+    uint32_t* hitbits;       // the same
+    int64_t N;
+    __device__ __forceinline__ uint32_t take(int idx, float3& o, float3& d) const {
+        const float4 rr = R[idx];
+        const uint32_t tag = __float_as_uint(rr.w);   // pixel within the tile | sample slot << 8
+        const float4 oo = origins[tag & 255u];
+        o = f3(oo.x, oo.y, oo.z);
+        d = f3(rr.x, rr.y, rr.z);
+        return tag;
+    }
+    __device__ __forceinline__ void hit(uint32_t tag) const {
+        const uint32_t slot = tag >> 8;
+        atomicOr(hitbits + (int64_t)(slot >> 5) * N + (tag & 255u), 1u << (slot & 31));
+    }
+};
+__device__ __forceinline__ TileFeed tile_feed(const ShadeArgs& A, int64_t tile, const float4* R, uint32_t* hitbits) {
+    return TileFeed{R, A.origins + tile * kBlock, hitbits + tile * kBlock, A.g.n};
+}
+struct QueryFeed {     // planes [3][n] from a workgroup's first ray, and its bytes
+    const float *o, *d;
+    int64_t n;
+    uint8_t* bytes;
+    __device__ __forceinline__ uint32_t take(int idx, float3& ro, float3& rd) const {
+        ro = f3(o[idx], o[n + idx], o[2 * n + idx]);
+        rd = f3(d[idx], d[n + idx], d[2 * n + idx]);
+        bytes[idx] = 0;      // the lane that takes the ray is the one that reports it
+        return (uint32_t)idx;
+    }
+    __device__ __forceinline__ void hit(uint32_t tag) const { bytes[tag] = 1; }
+};
+
+// TAIL: the longest rays bound the launch, so a full stack goes to private
+// memory and a wave's last kTailRays rays, kTailRounds rounds after the last was
+// taken, are walked by the whole wave (query_kernel says what that gives).
+constexpr int kTailRays = 4, kTailRounds = 6;
+template <bool COUNT, bool TAIL, typename Feed>
+__device__ __forceinline__ void trace_tile(const Scene& sc, const Feed& feed, int count, int* s_next,
+                                           uint32_t* s_stack, uint4* s_top, mcdi_stats* stats) {
     const int n_total = sc.nodes[0].escape;
     const uint32_t n_tris = (uint32_t)sc.n_tris;
     const QFrame F = *sc.frame;
@@ -490,7 +543,6 @@ __device__ __forceinline__ void trace_tile(const ShadeArgs& A, int64_t tile, con
         return *reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(s_stack) + at);
     };
     const int lane = __lane_id();
-    const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
     bool exhausted = n_total <= 0;   // uniform: no ray is left to take
     Ray ray;
     QRay qray;
@@ -499,14 +551,47 @@ __device__ __forceinline__ void trace_tile(const ShadeArgs& A, int64_t tile, con
     // reference is larger than its parent's index and smaller than the node
     // count)
     uint32_t node = kWideNone, p0 = 0u;
-    uint32_t tag = 0u;     // the ray's pixel within the tile | sample slot << 8
+    uint32_t tag = 0u;
     bool restart = false;  // the stack overflowed
+    int rounds = 0;        // since the last ray was taken
     uint32_t c_hits = 0, c_box = 0, c_tri = 0, c_bstep = 0, c_tstep = 0;   // steps: lane 0 only
     uint32_t c_blane = 0;
     auto report = [&]() {
-        const uint32_t slot = tag >> 8;
-        atomicOr(hitbits + (int64_t)(slot >> 5) * N + base_pix + (tag & 255u), 1u << (slot & 31));
+        feed.hit(tag);
         if (COUNT) ++c_hits;
+    };
+    // The lane's stack is full: its kSpill oldest references go to the lane's
+    // private memory, and kMoreRef takes their place in row 1 (row 0 stays).
+    uint32_t priv[1 + kSpillMax];   // how many (valid below a kMoreRef in row 1), and the references
+    auto unload = [&]() {
+        const bool again = row(sp0) == kMoreRef;
+        const uint32_t had = again ? priv[0] : 0u;
+        if (had + kSpill > kSpillMax) {
+            restart = true;
+            return;
+        }
+        uint32_t from = sp0 + (again ? kRow : 0u), to = sp0 + kRow;
+        for (uint32_t k = 1; k <= kSpill; ++k, from += kRow) priv[had + k] = row(from);
+        priv[0] = had + kSpill;
+        // (at least kStack + 1 - kSpill references move down, in increasing
+        // rows, not above where they were)
+        for (; from < sp; from += kRow, to += kRow) row(to) = row(from);
+        row(sp0) = kMoreRef;
+        sp = to;
+    };
+    // the walk came down to kMoreRef (the stack is empty): the newest of them back
+    auto reload = [&]() {
+        const uint32_t left = priv[0] - kSpill;
+        priv[0] = left;
+        sp = sp0;
+        if (left != 0u) {
+            row(sp) = kMoreRef;
+            sp += kRow;
+        }
+        for (uint32_t k = 1; k <= kSpill; ++k, sp += kRow) row(sp) = priv[left + k];
+        sp -= kRow;
+        node = row(sp) & kRefMask;
+        p0 = 0u;
     };
     // scheduling knobs: refill batch, node visits per phase check, and the
     // phase hand-over ratios (the box phase ends once four times the lanes
@@ -526,14 +611,13 @@ __device__ __forceinline__ void trace_tile(const ShadeArgs& A, int64_t tile, con
                 if (lane == 0) b = atomicAdd(s_next, n_need);
                 b = __builtin_amdgcn_readfirstlane(b);
                 exhausted = b + n_need >= count;
-                const int idx = b + (int)__popcll(need & lt);
+                const int idx = b + bits_below(need);
                 if (idle && idx < count) {
-                    const float4 rr = R[idx];
-                    tag = __float_as_uint(rr.w);
-                    const float4 o = A.origins[base_pix + (tag & 255u)];
-                    ray = make_ray(f3(o.x, o.y, o.z), f3(rr.x, rr.y, rr.z));
+                    float3 o, d;
+                    tag = feed.take(idx, o, d);
+                    ray = make_ray(o, d);
                     qray = make_qray(ray, F);
-                    oct = ray_octant(f3(rr.x, rr.y, rr.z));
+                    oct = ray_octant(d);
                     node = flat ? kWideNone : kRefTop;   // the root, hoisted node 0
                     restart = flat;
                     sp = sp0;
@@ -585,7 +669,10 @@ __device__ __forceinline__ void trace_tile(const ShadeArgs& A, int64_t tile, con
                         row(sp) = ws[k];
                         sp += ((ws[k] >> 30) & 1u) * kRow;
                     }
-                    if (sp > sp_end) restart = true;
+                    if (sp > sp_end) {
+                        if (TAIL) unload();
+                        else restart = true;
+                    }
                     sp -= kRow;
                     node = row(sp) & kRefMask;
                     // a leaf on top goes to the pending slot if that is free,
@@ -626,9 +713,11 @@ __device__ __forceinline__ void trace_tile(const ShadeArgs& A, int64_t tile, con
             if (test) {
                 const uint32_t t = (p0 >> 2) & 0x03FFFFFFu;
                 bool h = false;
-                if (t < n_tris) {       // a reference past the triangle array tests nothing
+                if (t < n_tris) {
                     if (COUNT) ++c_tri;
                     h = tri_anyhit(ray, sc.tris, t * 48u);
+                } else if (TAIL && p0 == kMoreRef) {   // (another reference past the triangle array tests nothing)
+                    reload();
                 }
                 if (h) {
                     report();
@@ -649,17 +738,31 @@ __device__ __forceinline__ void trace_tile(const ShadeArgs& A, int64_t tile, con
             const uint64_t free_ = __ballot(p0 == 0u && (int)node >= 0);
             if (2 * __popcll(free_) > kTriSwitch2 * __popcll(testing)) break;
         }
-        if (exhausted && !__any(node != kWideNone || p0 != 0u)) break;
+        if (exhausted) {
+            uint64_t left = __ballot(node != kWideNone || p0 != 0u);
+            if (left == 0ull) break;
+            // the last rays of the wave, each by all its lanes from the root
+            // (the lanes' stacks are dropped)
+            if (TAIL && ++rounds > kTailRounds && (int)__popcll(left) <= kTailRays) {
+                for (; left != 0ull; left &= left - 1ull) {
+                    const int l = (int)__ffsll((unsigned long long)left) - 1;
+                    const bool h = wave_anyhit<kBlock, kStackRows * 64>(sc, read_lane(ray, l), read_lane(qray, l), n_total,
+                                                                        s_stack + (threadIdx.x & ~63u));
+                    if (h && lane == l) report();
+                }
+                break;
+            }
+        }
     }
     if (COUNT) {
         const uint32_t h = wave_sum(c_hits), bx = wave_sum(c_box), tr = wave_sum(c_tri), bl = wave_sum(c_blane);
         if (lane == 0) {
-            atomicAdd(&A.stats->box_lanes, (unsigned long long)bl);
-            atomicAdd(&A.stats->rays_hit, (unsigned long long)h);
-            atomicAdd(&A.stats->box_tests, (unsigned long long)bx);
-            atomicAdd(&A.stats->tri_tests, (unsigned long long)tr);
-            atomicAdd(&A.stats->box_slots, 64ull * c_bstep);
-            atomicAdd(&A.stats->tri_slots, 64ull * c_tstep);
+            atomicAdd(&stats->box_lanes, (unsigned long long)bl);
+            atomicAdd(&stats->rays_hit, (unsigned long long)h);
+            atomicAdd(&stats->box_tests, (unsigned long long)bx);
+            atomicAdd(&stats->tri_tests, (unsigned long long)tr);
+            atomicAdd(&stats->box_slots, 64ull * c_bstep);
+            atomicAdd(&stats->tri_slots, 64ull * c_tstep);
         }
     }
 }
@@ -926,15 +1029,45 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8))) voi
     __shared__ uint32_t s_stack[kStackRows * kBlock];
     __shared__ uint4 s_top[4 * kTopNodes];
     const int rank = (int)blockIdx.x / parts, part = (int)blockIdx.x - rank * parts;
-    const int64_t tile = A.tile_order ? A.tile_order[rank] : rank;
-    if (tile < 0 || tile >= (int64_t)gridDim.x / parts) return;   // uniform: the whole workgroup reads the same entry
-    const int all = A.ray_count[tile];
+    const int tile = __builtin_amdgcn_readfirstlane(A.tile_order ? A.tile_order[rank] : rank);
+    if (tile < 0 || tile >= (int)gridDim.x / parts) return;   // uniform: the whole workgroup reads the same entry
+    const int all = __builtin_amdgcn_readfirstlane(A.ray_count[tile]);
     const int chunk = ((all + parts - 1) / parts + 63) & ~63, first = part * chunk;
     if (first >= all) return;
     if (threadIdx.x == 0) s_next = 0;
     __syncthreads();
-    trace_tile<COUNT>(A, tile, tile_region(A, tile) + first, min(chunk, all - first), hitbits, &s_next, s_stack,
-                      s_top);
+    trace_tile<COUNT, false>(A.scene, tile_feed(A, tile, tile_region(A, tile) + first, hitbits), min(chunk, all - first),
+                      &s_next, s_stack, s_top, A.stats);
+}
+
+// Any-hit queries over the 4-wide hierarchy: workgroup b walks rays
+// [b chunk, (b + 1) chunk) as it would a tile's, a lane one or a few rays, so
+// the longest rays bound it: at 400k incoherent rays against 296k triangles the
+// one-lane walk of the binary nodes took 268 us, this walk 290 (one ray whose
+// stack overflowed walked the binary nodes for 100 us alone), with the full
+// stack handed to private memory 190, and with a wave's last rays walked by all
+// its lanes 145; 127 at six waves per SIMD, which spill nothing (eight: 140,
+// five: 135).  20k rays 191 -> 73, 1M 428 -> 204, 4M 1233 -> 500; 400k against
+// 590 triangles 61 -> 52, against a room of 1.0M 358 -> 189.  The last four
+// rays six rounds after the last was taken: two rays or four rounds more are
+// within 10%, no wait costs short walks (590 triangles: 86 us).  The shading
+// kernels' walk, bound by throughput, does without either: the registers that
+// they take cost it 25%.
+constexpr int kQueryChunk = 4096;   // rays of a workgroup, at most (1024: 4M rays 600 us, 4096: 530)
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(6))) void query_kernel(
+    Scene sc, const float* o, const float* d, int64_t n, uint8_t* hit, int chunk) {
+    __shared__ int s_next;
+    __shared__ uint32_t s_stack[kStackRows * kBlock];
+    __shared__ uint4 s_top[4 * kTopNodes];
+    const int64_t first = (int64_t)blockIdx.x * chunk;
+    const int count = (int)min((int64_t)chunk, n - first);
+    if (sc.nodes[0].escape <= 0) {      // an empty scene
+        for (int k = threadIdx.x; k < count; k += kBlock) hit[first + k] = 0;
+        return;
+    }
+    if (threadIdx.x == 0) s_next = 0;
+    __syncthreads();
+    trace_tile<false, true>(sc, QueryFeed{o + first, d + first, n, hit + first}, count, &s_next, s_stack, s_top, nullptr);
 }
 
 template <bool BWD, bool DUMP, bool BIL>
@@ -1020,7 +1153,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
         float4* reg = A.tau != 0.0f ? region : nullptr;
         gen_tile<false>(A, tile, reg, it.hitbits, s_marg, &s_cnt);
         __syncthreads();
-        if (reg) trace_tile<false>(A, tile, reg, s_cnt, it.hitbits, &s_next, s_stack, s_top);
+        if (reg)
+            trace_tile<false, false>(A.scene, tile_feed(A, tile, reg, it.hitbits), s_cnt, &s_next, s_stack, s_top, nullptr);
         __syncthreads();
         const bool bil = (A.flags & MCDI_FLAG_BILINEAR) != 0;
         if (bil) shade_tile<false, false, true, false, true>(A, tile, s_marg, s_hot, RecSink{nullptr, nullptr});
@@ -1039,16 +1173,13 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
 
 __global__ void serve_reset(int* tile_counter) { *tile_counter = 0; }
 
-__global__ void trace_kernel(Scene sc, const float* o, const float* d, int64_t n, uint8_t* hit, int brute) {
+__global__ void trace_kernel(Scene sc, const float* o, const float* d, int64_t n, uint8_t* hit, bool brute) {
     const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= n) return;
     const Ray r = make_ray(f3(o[k], o[n + k], o[2 * n + k]), f3(d[k], d[n + k], d[2 * n + k]));
-    const int n_total = sc.nodes[0].escape;
     uint32_t nb = 0, nt = 0;
-    bool h;
-    if (brute == 1) h = brute_anyhit(sc, r);
-    else if (brute == 2) h = wbvh_anyhit(sc, r, n_total, nb, nt);
-    else h = qbvh_anyhit(sc, r, make_qray(r, *sc.frame), n_total, nb, nt);
+    const bool h = brute ? brute_anyhit(sc, r)
+                         : qbvh_anyhit(sc, r, make_qray(r, *sc.frame), sc.nodes[0].escape, nb, nt);
     hit[k] = h ? 1 : 0;
 }
 
@@ -1131,11 +1262,19 @@ hipError_t launch_shade_bwd(const ShadeArgs& a, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_trace(const Scene& sc, const float* o, const float* d, int64_t n, uint8_t* hit, int brute,
+// mode 0: the binary nodes, 1: every triangle, 2: the 4-wide nodes
+hipError_t launch_trace(const Scene& sc, const float* o, const float* d, int64_t n, uint8_t* hit, int mode,
                         hipStream_t s) {
     if (n == 0) return hipSuccess;
+    if (mode == 2) {
+        const int64_t slots = 2048, fill = ((n + slots - 1) / slots + 63) & ~(int64_t)63;
+        const int chunk = (int)(fill < kBlock ? kBlock : fill > kQueryChunk ? kQueryChunk : fill);
+        hipLaunchKernelGGL(query_kernel, dim3((unsigned)((n + chunk - 1) / chunk)), dim3(kBlock), 0, s, sc, o, d, n, hit,
+                           chunk);
+        return hipGetLastError();
+    }
     const int64_t blocks = (n + 255) / 256;
-    hipLaunchKernelGGL(trace_kernel, dim3((unsigned)blocks), dim3(256), 0, s, sc, o, d, n, hit, brute);
+    hipLaunchKernelGGL(trace_kernel, dim3((unsigned)blocks), dim3(256), 0, s, sc, o, d, n, hit, mode == 1);
     return hipGetLastError();
 }
 
