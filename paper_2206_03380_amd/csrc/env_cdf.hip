@@ -86,7 +86,7 @@ __host__ __device__ constexpr int row_stride(int W) { return W + 2; }
 
 // rowsum: [H] row sums, [H] the total (marginal_kernel), [H + 1 ..) the rows' sines
 __global__ __launch_bounds__(kRowThreads) void rows_kernel(const float* env, int H, int W, int G, int rows, float* cond,
-                                                           double* rowsum, int32_t* guide, int32_t* n_hot) {
+                                                           double* rowsum, uint16_t* guide, int32_t* n_hot) {
     extern __shared__ double smem[];  // [rows][row_stride(W)]
     __shared__ double s_sum[kRowsPer], s_sin[kRowsPer];
     const int i0 = blockIdx.x * rows, nr = min(rows, H - i0), S = row_stride(W);
@@ -127,7 +127,7 @@ __global__ __launch_bounds__(kRowThreads) void rows_kernel(const float* env, int
             const int mid = (lo + hi) >> 1;
             if (entry(r, mid) <= x) lo = mid; else hi = mid;
         }
-        guide[(size_t)(i0 + r) * (G + 1) + g] = lo;
+        guide[(size_t)(i0 + r) * (G + 1) + g] = (uint16_t)lo;
     }
 }
 
@@ -214,21 +214,15 @@ hipError_t launch_env_mix(const float4* rgb, const float4* dens, int64_t n, floa
     return hipGetLastError();
 }
 
-// Whether light draws read a cell's candidates in one go (cdf_find_row): for
-// conditional tables larger than one XCD's L2 (4 MB), where a line read by
-// one binary-search probe is often gone by the next.  A table that stays in
-// the cache is searched faster by the binary search.
-int env_row_window(int H, int W) {
+// Guide cells per row, at most 1024: about eight columns per cell, sixteen where
+// the conditional table is larger than one XCD's L2 (4 MB): draws wait for its
+// lines there, and a guide of half the size leaves them more of the cache.
+// Generation and forward shading of 4.2M pixels at 32 spp, 4, 8, 16 and 32
+// columns: 512 x 1024 probe 3.43, 3.31, 3.45 ms (4, 8, 16), 1024 x 2048 probe
+// 4.83, 4.37, 4.34, 4.72 ms.
+int env_guide_cells(int H, int W) {
     constexpr double kL2Bytes = 4 << 20;
-    return (double)H * (W + 1) * sizeof(float) > kL2Bytes ? 1 : 0;
-}
-
-// Guide cells per row, at most 1024: about eight columns per cell for the
-// binary search; sixteen with the candidate window, whose guide (a sixteenth
-// of the rows' size) then stays in the L2 cache (on a 2048-column probe finer
-// guides measured slower).
-int env_guide_cells(int W, int win) {
-    const int cols = win ? 16 : 8;
+    const int cols = (double)H * (W + 1) * sizeof(float) > kL2Bytes ? 16 : 8;
     int G = 1;
     while (cols * G <= W && G < 1024) G *= 2;
     return G;

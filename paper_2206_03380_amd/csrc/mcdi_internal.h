@@ -128,11 +128,10 @@ struct EnvView {
     const int32_t* hot_slot;       // [H*W] LDS slot of a hot texel or -1
     const int32_t* hot_texel;      // [kHotMax] texel of each slot
     const int32_t* n_hot;          // number of hot texels (<= kHotMax)
-    const int32_t* guide;          // [H][G+1] search guide of the conditional rows
+    const uint16_t* guide;         // [H][G+1] search guide of the conditional rows
     int32_t G;                     // guide cells per row (power of two)
     const float4* tex;             // [H*W] (r, g, b, pdf): radiance and density in one line
     const float* pdf;              // [H*W] the density alone (tex.w), a quarter of tex's lines
-    int32_t win;                   // 1: row searches read the cell's candidates in one go
     const uint8_t* dclass;         // [(H*W + 3) / 4] density classes, 2 bits per texel
 };
 
@@ -212,7 +211,7 @@ struct EnvTables {
     float *cond, *marg, *pdf;
     double* rowsum;            // [2 H + 1] scratch: row sums, the total, the rows' sines
     int32_t* light_enabled;
-    int32_t* guide;
+    uint16_t* guide;
     int32_t G;
     float4* tex;
     uint8_t* dclass;
@@ -221,8 +220,7 @@ struct EnvTables {
 hipError_t launch_env_tables(const float* env, int H, int W, const EnvTables& t, hipStream_t s);
 // Search guide of the conditional CDF rows: guide[i][g] = the largest column
 // k <= W-1 with cond[i][k] <= g / G, for g = 0..G.
-int env_row_window(int H, int W);
-int env_guide_cells(int W, int win);
+int env_guide_cells(int H, int W);
 // out[k] = (rgb[k].xyz, dens[k].w)
 hipError_t launch_env_mix(const float4* rgb, const float4* dens, int64_t n, float4* out, hipStream_t s);
 // forward = gen_rays -> trace_rays -> shade; hit bits are produced by the

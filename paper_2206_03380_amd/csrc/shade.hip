@@ -29,10 +29,8 @@ namespace mcdi {
 namespace {
 
 // visible-normal sample (Heitz 2018), local frame
-__device__ __forceinline__ float3 sample_vndf(const Pixel& P, float u1, float u2) {
-    const float r = sqrtf(u1);
-    float sp, cp;
-    sincospif(2.0f * u2, &sp, &cp);
+// (r, sp, cp: sqrt(u1), sin and cos of 2 pi u2)
+__device__ __forceinline__ float3 sample_vndf(const Pixel& P, float r, float sp, float cp) {
     const float a1 = r * cp;
     float a2 = r * sp;
     const float s = 0.5f * (1.0f + P.vh.z);
@@ -75,8 +73,7 @@ struct BwdAcc {
 //  kDrawBwd  adjoint: the density from the radiance table (the evaluation
 //            reads that line again) and always the binary row search, which
 //            needs fewer registers than the adjoint has to spare.
-// The other two read the row's candidates in one go (cdf_find_row) where the
-// tables ask for it (env.win).
+// The other two read the row's candidates in one go (cdf_find_row).
 enum DrawMode { kDrawGen, kDrawFwd, kDrawBwd };
 
 template <int MODE>
@@ -84,11 +81,11 @@ __device__ __forceinline__ bool draw_light(const ShadeArgs& A, const Pixel& P, c
                                            Sample& S) {
     const int H = A.env.H, W = A.env.W;
     const float x0 = u01(r0.x), x1 = u01(r0.y);
-    const int i = cdf_find(s_marg, H, x0);
+    const int i = cdf_find_padded(s_marg, search_size(H), x0);
     const float* crow = A.env.cond + (size_t)i * (W + 1);
     float c0, c1;
     int j;
-    if (MODE != kDrawBwd && A.env.win) {
+    if (MODE != kDrawBwd) {
         j = cdf_find_row(crow, A.env.guide + (size_t)i * (A.env.G + 1), A.env.G, x1, c0, c1);
     } else {
         j = cdf_find_guided(crow, A.env.guide + (size_t)i * (A.env.G + 1), A.env.G, x1);
@@ -98,24 +95,28 @@ __device__ __forceinline__ bool draw_light(const ShadeArgs& A, const Pixel& P, c
     const float m0 = s_marg[i], m1 = s_marg[i + 1];
     S.y = (float)i + (x0 - m0) / (m1 - m0);
     S.x = (float)j + (x1 - c0) / (c1 - c0);
-    const float v = S.y / (float)H;
-    const float u = S.x / (float)W;
+    const float v = div_small(S.y, (float)H, 1.0f / (float)H);
+    const float u = div_small(S.x, (float)W, 1.0f / (float)W);
     float st, ct, sp, cp;
     sincospif(v, &st, &ct);
     sincospif(2.0f * u, &sp, &cp);
     S.w = f3(st * cp, ct, st * sp);
     S.texel = i * W + j;
+    bool tiny = false;
     if (MODE == kDrawFwd) {
         S.tx = A.env.tex[S.texel];
     } else if (MODE == kDrawGen) {
         // generation only asks whether the density is positive: the
         // texel's class answers it except for tiny densities (class 2)
         const uint32_t cls = (A.env.dclass[S.texel >> 2] >> (2 * (S.texel & 3))) & 3u;
-        S.tx.w = cls == 2u ? A.env.pdf[S.texel] : (float)cls;
+        tiny = cls == 2u;
+        S.tx.w = tiny ? A.env.pdf[S.texel] : (float)cls;
     } else {
         S.tx.w = A.env.tex[S.texel].w;
     }
-    S.pL = st > 0.0f ? S.tx.w / (2.0f * kPi * kPi * st) : 0.0f;
+    // (generation: a normal density over at most 2 pi^2 is positive)
+    if (MODE == kDrawGen && !tiny) S.pL = st > 0.0f ? S.tx.w : 0.0f;
+    else S.pL = st > 0.0f ? S.tx.w / (2.0f * kPi * kPi * st) : 0.0f;
     S.wl = f3(dot(S.w, P.t), dot(S.w, P.b), dot(S.w, P.n));
     return S.pL > 0.0f;
 }
@@ -124,13 +125,14 @@ __device__ __forceinline__ bool draw_light(const ShadeArgs& A, const Pixel& P, c
 __device__ __forceinline__ bool draw_bsdf(const Pixel& P, uint4 r0, uint4 r1, Sample& S) {
     const float x2 = u01(r0.z), x4 = u01(r1.x), x5 = u01(r1.y);
     const bool cosl = x2 < P.q;
+    // both lobes map the unit disk: a wave usually draws from both
+    const float rr = sqrtf(x4);
+    float sp, cp;
+    sincospif(2.0f * x5, &sp, &cp);
     if (cosl) {
-        const float rr = sqrtf(x4);
-        float sp, cp;
-        sincospif(2.0f * x5, &sp, &cp);
         S.wl = f3(rr * cp, rr * sp, sqrtf(fmaxf(0.0f, 1.0f - x4)));
     } else {
-        S.wl = sample_vndf(P, x4, x5);
+        S.wl = sample_vndf(P, rr, sp, cp);
     }
     S.w = normalize(S.wl.x * P.t + S.wl.y * P.b + S.wl.z * P.n);
     S.pL = 0.0f;
@@ -338,8 +340,14 @@ __device__ __forceinline__ uint32_t even_bits(uint32_t x) {
     return x;
 }
 
+// the marginal CDF in LDS: H + 1 entries, padded for the search (and to 16 bytes)
+__host__ __device__ inline int marg_entries(int H) {
+    const int p = search_size(H);
+    return ((p > H + 1 ? p : H + 1) + 3) & ~3;
+}
 __device__ __forceinline__ void stage_marg(const ShadeArgs& A, float* s_marg) {
-    for (int k = threadIdx.x; k <= A.env.H; k += blockDim.x) s_marg[k] = A.env.marg[k];
+    const int H = A.env.H, n = marg_entries(H);
+    for (int k = threadIdx.x; k < n; k += blockDim.x) s_marg[k] = k <= H ? A.env.marg[k] : 1.0f;
 }
 
 // ---------------------------------------------------------------------------
@@ -1075,7 +1083,7 @@ __device__ __forceinline__ void shade_body(const ShadeArgs& A) {
     extern __shared__ float smem[];
     __shared__ uint32_t s_rec;
     float* s_marg = smem;
-    float* s_hot = smem + ((A.env.H + 1 + 3) & ~3);
+    float* s_hot = smem + marg_entries(A.env.H);
     stage_marg(A, s_marg);
     if (BWD) hot_zero(s_hot);
     if (threadIdx.x == 0) s_rec = 0u;
@@ -1127,7 +1135,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     __shared__ uint32_t s_stack[kStackRows * kBlock];
     __shared__ uint4 s_top[4 * kTopNodes];
     float* s_hot = smem;                     // 3 * kHotMax
-    float* s_marg = smem + 3 * kHotMax;      // H + 1 of the current item
+    float* s_marg = smem + 3 * kHotMax;      // marg_entries(H) of the current item
     float4* region = scratch + (size_t)blockIdx.x * (size_t)(2 * spp_max * kBlock);
     while (true) {
         if (threadIdx.x == 0) {
@@ -1204,7 +1212,7 @@ static int trace_parts(const ShadeArgs& a) {
     return (int)(p < most ? p : most);
 }
 
-static size_t marg_lds(const ShadeArgs& a) { return sizeof(float) * (size_t)((a.env.H + 1 + 3) & ~3); }
+static size_t marg_lds(const ShadeArgs& a) { return sizeof(float) * (size_t)marg_entries(a.env.H); }
 
 hipError_t launch_gen_rays(const ShadeArgs& a, uint32_t* hitbits, hipStream_t s) {
     if (a.stats)
@@ -1240,7 +1248,7 @@ hipError_t launch_shade_fwd(const ShadeArgs& a, hipStream_t s) {
 hipError_t launch_serve(const ServeItem* items_dev, int n_items, int64_t total_tiles, int* tile_counter,
                         float4* scratch, int spp_max, int n_workgroups, int max_H, hipStream_t s) {
     hipLaunchKernelGGL(serve_reset, dim3(1), dim3(1), 0, s, tile_counter);
-    const size_t lds = sizeof(float) * (3 * kHotMax + (size_t)max_H + 1);
+    const size_t lds = sizeof(float) * (3 * kHotMax + (size_t)marg_entries(max_H));
     hipLaunchKernelGGL(serve_kernel, dim3(n_workgroups), dim3(kBlock), lds, s, items_dev, n_items, total_tiles,
                        tile_counter, scratch, spp_max);
     return hipGetLastError();
