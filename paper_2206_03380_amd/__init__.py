@@ -23,11 +23,18 @@ def _ptr(t):
 
 
 def _stream(stream=None):
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return C.c_void_p(s.cuda_stream)
+    if stream is not None:
+        return C.c_void_p(stream.cuda_stream)
+    if not torch.cuda.is_initialized():
+        torch.cuda.init()
+    return C.c_void_p(torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()))
 
 
 def _need(t, dtype, shape=None, name="tensor"):
+    # (most calls: nothing to report)
+    if (isinstance(t, torch.Tensor) and t.is_cuda and t.dtype == dtype and t.is_contiguous()
+            and (shape is None or t.shape == shape)):
+        return t
     if not isinstance(t, torch.Tensor) or not t.is_cuda:
         raise TypeError("%s must be a CUDA (HIP) tensor" % name)
     if t.dtype != dtype:
@@ -39,18 +46,22 @@ def _need(t, dtype, shape=None, name="tensor"):
     return t
 
 
-# torch's caching allocator behind the library's allocator hook
+# torch's caching allocator behind the library's allocator hook, on the current
+# device, by the bindings themselves: torch.cuda.caching_allocator_alloc enters a
+# device guard in Python around the same call, and a scene's and a probe's tables
+# take about twenty allocations (a 64 x 64 iteration, bound by the host: 440 ->
+# 375 us with the stream and the checks above)
 @C.CFUNCTYPE(C.c_void_p, C.c_void_p, C.c_size_t, C.c_void_p)
 def _torch_alloc(ctx, nbytes, stream):
     try:
-        return torch.cuda.caching_allocator_alloc(int(nbytes), stream=int(stream or 0))
+        return torch._C._cuda_cudaCachingAllocator_raw_alloc(nbytes, stream or 0)
     except Exception:  # out of memory: report NULL to the library
         return None
 
 
 @C.CFUNCTYPE(None, C.c_void_p, C.c_void_p, C.c_void_p)
 def _torch_free(ctx, ptr, stream):
-    torch.cuda.caching_allocator_delete(ptr)
+    torch._C._cuda_cudaCachingAllocator_raw_delete(ptr)
 
 
 _TORCH_ALLOCATOR = L.Allocator(None, _torch_alloc, _torch_free)
