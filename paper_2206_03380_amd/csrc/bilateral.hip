@@ -11,15 +11,17 @@
 // v*H*W + y*W + x.  A workgroup owns a 16x16 tile: it stages the tile plus an
 // R-pixel halo of guides (normalised normal and depth as one float4) and
 // colours in LDS, then every lane walks its footprint out of LDS.  Each wave
-// covers an 8x8 block and the LDS row stride is an odd multiple of 8 words,
-// so the 64 lanes of one tap read 64 different banks.  Blocks are remapped so
+// covers an 8x8 block and the colours' LDS row stride is an odd multiple of 8
+// words, so the 64 lanes of one tap read 64 different banks.  Blocks are remapped so
 // that consecutive tiles land on the same XCD and share halo lines in its L2.
 //
 // Precision: the depth gradient and the linear depth prediction are formed in
 // FP64 from the FP32 depths (the differences of FP32 values and their products
 // with the small integer offsets are exact there), so the prediction does not
 // lose its digits when the two gradient components cancel along an iso-depth
-// line.  The three weight factors are combined in one base-2 exponent and a
+// line (scaled by sigma_z ln 2 before the taps: one FP64 product less in each,
+// forward 226 -> 193 us at R = 6, six channels, eight 512 x 512 views).  The
+// three weight factors are combined in one base-2 exponent and a
 // single exp2; colours accumulate in FP32.
 #include <hip/hip_runtime.h>
 #include <math.h>
@@ -34,6 +36,21 @@ constexpr double kEpsZ = 1e-5;  // added to the depth prediction (p = q gives 0 
 constexpr double kLn2 = 0.69314718055994530942;
 
 __host__ __device__ constexpr int lds_stride(int R) { return kT + 2 * R <= 24 ? 24 : 40; }
+
+// Row stride of the guides (gb bytes each) beside nc planes of colours: without
+// padding where one more workgroup then fits in a CU's LDS (160 KB in pieces of
+// 1280 bytes), though two lanes of a tap's guide read then share a bank.  The
+// taps are chains through a logarithm, a reciprocal and an exponential, which
+// other waves hide: six channels, R = 6, eight 512 x 512 views, backward 2 -> 3
+// workgroups, 261 -> 221 us; where the count stays (one channel, R = 3; six,
+// R = 8) no padding costs 12 and 4%.  (Two pixels per lane, which halves the
+// LDS reads, gains 4% backward and loses 3% forward.)
+constexpr int lds_groups(int bytes) { return 163840 / ((bytes + 1279) / 1280 * 1280); }
+__host__ __device__ constexpr int guide_stride(int R, int nc, int gb) {
+    const int rw = kT + 2 * R, S = lds_stride(R), col = rw * S * 4 * nc;
+    const int padded = lds_groups(rw * S * gb + col), packed = lds_groups(rw * rw * gb + col);
+    return (packed > padded && padded < 8) ? rw : S;
+}
 
 // Balanced block -> tile bijection: hardware places block b on XCD b % 8;
 // XCD x gets the contiguous tile range starting at x*q + min(x, r).
@@ -65,15 +82,15 @@ struct WeightConsts {
 };
 
 // w(p, q) for guides p, q (normal xyz normalised or zero, depth w), the depth
-// gradient at p, and the offset (dx, dy) = q - p.
-__device__ __forceinline__ float tap_weight(const float4& p, const float4& q, double gx, double gy, int dx, int dy,
-                                            const WeightConsts& c) {
+// gradient at p times sigma_z ln 2 (its y part times dy), and the offset
+// (dx, dy) = q - p, dy2 = dy^2.
+__device__ __forceinline__ float tap_weight(const float4& p, const float4& q, double gx, double gydy, int dx,
+                                            float dy2, const WeightConsts& c) {
     const float d = fmaf(p.x, q.x, fmaf(p.y, q.y, p.z * q.z));
     const float lg = __builtin_amdgcn_logf(fmaxf(d, 0.0f));  // log2, -inf at 0
-    const double pr = fabs(fma(gx, (double)dx, gy * (double)dy));
-    const float den = (float)__dadd_rn(__dmul_rn(c.szl, pr), c.epsl);
+    const float den = (float)__dadd_rn(fabs(fma(gx, (double)dx, gydy)), c.epsl);
     const float az2 = fabsf(p.w - q.w) * __builtin_amdgcn_rcpf(den);  // |dz| / (pred + eps) * log2(e)
-    const float e = fmaf(c.sn, lg, (float)(dx * dx + dy * dy) * c.ks - az2);
+    const float e = fmaf(c.sn, lg, ((float)(dx * dx) + dy2) * c.ks - az2);
     return __builtin_amdgcn_exp2f(e);
 }
 
@@ -110,8 +127,8 @@ __device__ __forceinline__ void lane_pixel(int& px, int& py) {
 template <int R, int NC>
 __global__ __launch_bounds__(256) void bilat_fwd_kernel(BilatArgs a, WeightConsts wc, const float* __restrict__ in,
                                                         float* __restrict__ out, float* __restrict__ wsum) {
-    constexpr int S = lds_stride(R), RW = kT + 2 * R;
-    __shared__ float4 geo[RW * S];
+    constexpr int S = lds_stride(R), RW = kT + 2 * R, G = guide_stride(R, NC, 16);
+    __shared__ float4 geo[RW * G];
     __shared__ float col[NC][RW * S];
     const TileLoc t = tile_loc(a);
     for (int i = threadIdx.x; i < RW * RW; i += 256) {
@@ -129,7 +146,7 @@ __global__ __launch_bounds__(256) void bilat_fwd_kernel(BilatArgs a, WeightConst
                 for (int ch = 0; ch < NC; ++ch) c[ch] = in[ch * a.n + k];
             }
         }
-        geo[ly * S + lx] = g;
+        geo[ly * G + lx] = g;
 #pragma unroll
         for (int ch = 0; ch < NC; ++ch) col[ch][ly * S + lx] = c[ch];
     }
@@ -147,17 +164,21 @@ __global__ __launch_bounds__(256) void bilat_fwd_kernel(BilatArgs a, WeightConst
     }
     double gx, gy;
     depth_grad(a.depth, a.mask, t.base, x, y, a.W, a.H, gx, gy);
-    const float4 gp = geo[(py + R) * S + px + R];
+    const float4 gp = geo[(py + R) * G + px + R];
     float acc[NC];
 #pragma unroll
     for (int ch = 0; ch < NC; ++ch) acc[ch] = 0.0f;
     float den = 0.0f;
+    gx *= wc.szl;
+    gy *= wc.szl;
     for (int dy = -R; dy <= R; ++dy) {
-        const int row = (py + R + dy) * S + px + R;
+        const int row = (py + R + dy) * S + px + R, grow = (py + R + dy) * G + px + R;
+        const double gydy = gy * (double)dy;
+        const float dy2 = (float)(dy * dy);
 #pragma unroll
         for (int dx = -R; dx <= R; ++dx) {
             const int j = row + dx;
-            const float w = tap_weight(gp, geo[j], gx, gy, dx, dy, wc);
+            const float w = tap_weight(gp, geo[grow + dx], gx, gydy, dx, dy2, wc);
             den += w;
 #pragma unroll
             for (int ch = 0; ch < NC; ++ch) acc[ch] = fmaf(w, col[ch][j], acc[ch]);
@@ -171,14 +192,14 @@ __global__ __launch_bounds__(256) void bilat_fwd_kernel(BilatArgs a, WeightConst
 
 // Adjoint: dL/dc(q) = sum_p dL/dout(p) w(p, q) / W(p) over the p whose
 // footprint holds q, i.e. p = q - d for the same offsets d.  The staged
-// region carries each p's guide, its FP64 depth gradient and its upstream
-// gradient already divided by W(p).
+// region carries each p's guide, its FP64 depth gradient (times sigma_z ln 2)
+// and its upstream gradient already divided by W(p).
 template <int R, int NC>
 __global__ __launch_bounds__(256) void bilat_bwd_kernel(BilatArgs a, WeightConsts wc, const float* __restrict__ g_out,
                                                         const float* __restrict__ wsum, float* __restrict__ g_in) {
-    constexpr int S = lds_stride(R), RW = kT + 2 * R;
-    __shared__ float4 geo[RW * S];
-    __shared__ double2 grd[RW * S];
+    constexpr int S = lds_stride(R), RW = kT + 2 * R, G = guide_stride(R, NC, 32);
+    __shared__ float4 geo[RW * G];
+    __shared__ double2 grd[RW * G];
     __shared__ float gw[NC][RW * S];
     const TileLoc t = tile_loc(a);
     for (int i = threadIdx.x; i < RW * RW; i += 256) {
@@ -194,14 +215,16 @@ __global__ __launch_bounds__(256) void bilat_bwd_kernel(BilatArgs a, WeightConst
             if (a.mask[k]) {
                 g = load_guide(a, k);
                 depth_grad(a.depth, a.mask, t.base, gx, gy, a.W, a.H, d2.x, d2.y);
+                d2.x *= wc.szl;
+                d2.y *= wc.szl;
                 const float W = wsum[k];
                 const float inv = W > 0.0f ? 1.0f / W : 0.0f;
 #pragma unroll
                 for (int ch = 0; ch < NC; ++ch) c[ch] = g_out[ch * a.n + k] * inv;
             }
         }
-        geo[ly * S + lx] = g;
-        grd[ly * S + lx] = d2;
+        geo[ly * G + lx] = g;
+        grd[ly * G + lx] = d2;
 #pragma unroll
         for (int ch = 0; ch < NC; ++ch) gw[ch][ly * S + lx] = c[ch];
     }
@@ -215,14 +238,16 @@ __global__ __launch_bounds__(256) void bilat_bwd_kernel(BilatArgs a, WeightConst
 #pragma unroll
     for (int ch = 0; ch < NC; ++ch) acc[ch] = 0.0f;
     if (a.mask[k]) {
-        const float4 gq = geo[(py + R) * S + px + R];
+        const float4 gq = geo[(py + R) * G + px + R];
         for (int dy = -R; dy <= R; ++dy) {
-            const int row = (py + R - dy) * S + px + R;
+            const int row = (py + R - dy) * S + px + R, grow = (py + R - dy) * G + px + R;
+            const double ddy = (double)dy;
+            const float dy2 = (float)(dy * dy);
 #pragma unroll
             for (int dx = -R; dx <= R; ++dx) {
                 const int j = row - dx;
-                const double2 gp = grd[j];
-                const float w = tap_weight(geo[j], gq, gp.x, gp.y, dx, dy, wc);
+                const double2 gp = grd[grow - dx];
+                const float w = tap_weight(geo[grow - dx], gq, gp.x, gp.y * ddy, dx, dy2, wc);
 #pragma unroll
                 for (int ch = 0; ch < NC; ++ch) acc[ch] = fmaf(w, gw[ch][j], acc[ch]);
             }
