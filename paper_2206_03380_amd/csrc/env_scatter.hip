@@ -264,8 +264,8 @@ __global__ __launch_bounds__(256) void scatter_kernel(EnvScatter p) {
 
 // acc holds A accumulators of 3 channels per texel of the bucket, [a][texel][3]:
 // A = 1 (nearest) or the four taps (bilinear), flushed into g_env or acc4
-template <bool BIL>
-__global__ __launch_bounds__(256) void accumulate_kernel(EnvScatter p) {
+template <bool BIL, int T>
+__global__ __launch_bounds__(T) void accumulate_kernel(EnvScatter p) {
     extern __shared__ long long acc[];   // [A][3 << shift] fixed point (or float in the same space)
     constexpr int A = BIL ? 4 : 1;
     const uint32_t R = p.start[p.K];
@@ -292,19 +292,19 @@ __global__ __launch_bounds__(256) void accumulate_kernel(EnvScatter p) {
         const int S = 62 - chunk_log2 - ex;
         const double scale = ldexp(1.0, S), unscale = ldexp(1.0, -S);
         for (int a = 0; a < A; ++a)
-            for (int k = threadIdx.x; k < 3 * n_tex; k += 256) {
+            for (int k = threadIdx.x; k < 3 * n_tex; k += T) {
                 if (fixed) acc[a * slab + k] = 0;
                 else accf[2 * (a * slab + k)] = 0.0f;
             }
         __syncthreads();
-        for (uint32_t i = s + threadIdx.x; i < e; i += 1024) {
+        for (uint32_t i = s + threadIdx.x; i < e; i += 4 * T) {
             RecT<BIL> r[4];
 #pragma unroll
             for (int j = 0; j < 4; ++j)
-                if (i + 256 * j < e) r[j] = RecT<BIL>::load(p.sorted, i + 256 * j);
+                if (i + T * j < e) r[j] = RecT<BIL>::load(p.sorted, i + T * j);
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                if (i + 256 * j < e) {
+                if (i + T * j < e) {
                     const int k = 3 * (int)(r[j].key() - (uint32_t)first);
                     float w[A];
                     if (BIL) {
@@ -335,7 +335,7 @@ __global__ __launch_bounds__(256) void accumulate_kernel(EnvScatter p) {
         __syncthreads();
         for (int a = 0; a < A; ++a) {
             float* g = BIL ? p.acc4 + ((size_t)a * p.n_texels + first) * 3 : p.g_env + 3 * (size_t)first;
-            for (int k = threadIdx.x; k < 3 * n_tex; k += 256) {
+            for (int k = threadIdx.x; k < 3 * n_tex; k += T) {
                 const float v = fixed ? (float)((double)acc[a * slab + k] * unscale) : accf[2 * (a * slab + k)];
                 if (v != 0.0f) atomicAdd(g + k, v);
             }
@@ -454,11 +454,18 @@ static hipError_t launch_env_scatter_t(const EnvScatter& p, hipStream_t s) {
     const unsigned grid = accumulate_grid(p.cap);
     const size_t lds_acc = sizeof(long long) * (3u << p.shift) * (BIL ? 4 : 1);
     if (lds_acc > 65536) {   // above the default dynamic LDS limit
-        const hipError_t e = hipFuncSetAttribute((const void*)accumulate_kernel<BIL>,
+        const hipError_t e = hipFuncSetAttribute((const void*)accumulate_kernel<BIL, 1024>,
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_acc);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(accumulate_kernel<BIL>, dim3(grid), dim3(256), lds_acc, s, p);
+    // 256 threads beside a 24 KB copy (24 waves per CU); larger copies (48 or
+    // 96 KB: probes past 1M texels, the bilinear taps) leave one to three
+    // workgroups per CU, which then have 1024 threads (6.4M bilinear samples
+    // 178 -> 109 us)
+    if (lds_acc <= 32768)
+        hipLaunchKernelGGL((accumulate_kernel<BIL, 256>), dim3(grid), dim3(256), lds_acc, s, p);
+    else
+        hipLaunchKernelGGL((accumulate_kernel<BIL, 1024>), dim3(grid), dim3(1024), lds_acc, s, p);
     if (BIL) {
         const int64_t n = 3 * (int64_t)p.H * p.W;
         hipLaunchKernelGGL(gather_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, p);
