@@ -1123,7 +1123,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3))) voi
 // workgroup takes the next tile from a global counter and runs generation,
 // traversal, the forward evaluation and (for gradient requests) the adjoint
 // on it; it stops when the tiles run out, so every wave exits.  Four waves
-// per SIMD (128 VGPRs, 84 bytes spilled): left to itself the compiler takes
+// per SIMD (128 VGPRs, 112 bytes spilled): left to itself the compiler takes
 // 171 registers for the adjoint's stretch and the whole launch runs at two
 // waves, the traversal's included; on the serving mix four waves served 16%
 // more requests per second, five and six (more spills) fewer.
