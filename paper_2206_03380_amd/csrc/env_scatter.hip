@@ -23,11 +23,11 @@
 // the bucket's largest |value|, found by the histogram step), so with scale
 // 2^(62-c-e) the int64 sum cannot overflow, and each record is rounded by at
 // most 2^-(63-c-e), i.e. < 2^-(63-c) of the bucket maximum.  The chunks split
-// the records actually written (R, read on the device) over the launch's
-// workgroups: a chunk holds max(2^10, ceil(R / workgroups)) records and c is
-// the ceiling of its log2.  There are min(2048, ceil(capacity / 2^10))
-// workgroups and R <= capacity <= 2^30, so 10 <= c <= 19: the rounding of one
-// record is below 2^-44 of the bucket maximum.  (Sizing the chunks by the
+// the records actually written (R, read on the device) and their buckets, each
+// counted as kBucketCost records, over the launch's workgroups; c is the ceiling
+// of the log2 of a chunk's records.  There are min(2048, ceil(capacity / 2^10))
+// workgroups and R <= capacity <= 2^30, so c <= 20 (19 up to 2^30 - 2^22 records): the rounding of one
+// record is below 2^-43 of the bucket maximum.  (Sizing the chunks by the
 // capacity instead left most workgroups idle when most samples add nothing:
 // on the 1.0M-triangle room 95% of the shadow rays are blocked, and 8.7M
 // records filled 67 chunks of a 268M-record capacity.)  A bucket with a non-finite value takes
@@ -56,7 +56,14 @@ constexpr int kMaxShift = 12;          // 4096 texels: 96 KB of LDS per fixed-po
 constexpr int kMaxBuckets = 4096;      // 4096 x 4096 texels at most
 constexpr int kGridMax = 2048;
 constexpr int kBatch = 1024;           // records per LDS sort batch
-constexpr uint32_t kChunkMin = 1024;   // sorted records per accumulate workgroup, at least
+constexpr uint32_t kChunkMin = 1024;   // sorted records per accumulate workgroup, at least (with:)
+// Records that clearing and flushing a bucket's sums count as in the split of
+// the accumulation.  Split by records alone, a few workgroups got hundreds of
+// buckets of a few records each and the launch waited for them: 8.7M records
+// over 2,048 buckets (a room with four windows) 448 us; the adjoint's call there
+// 2.41 ms, with 32, 256, 1024 and 4096 records a bucket 2.19, 2.06, 2.03 and
+// 2.01 ms, even loads (15M records, 128 buckets) unchanged.
+constexpr uint32_t kBucketCost = 1024;
 
 __device__ __forceinline__ uint32_t rec_texel(const float4& r) { return __float_as_uint(r.x); }
 
@@ -268,14 +275,35 @@ template <bool BIL, int T>
 __global__ __launch_bounds__(T) void accumulate_kernel(EnvScatter p) {
     extern __shared__ long long acc[];   // [A][3 << shift] fixed point (or float in the same space)
     constexpr int A = BIL ? 4 : 1;
-    const uint32_t R = p.start[p.K];
-    const uint32_t chunk = max(kChunkMin, (uint32_t)(((uint64_t)R + gridDim.x - 1) / gridDim.x));
+    // this workgroup's piece [v0, v1) of the records with kBucketCost entries
+    // before each bucket's, and the records in it
+    const int K = p.K;
+    const uint32_t R = p.start[K];
+    const uint64_t all = (uint64_t)R + (uint64_t)kBucketCost * (uint64_t)K;
+    const uint64_t chunk = max((uint64_t)kChunkMin, (all + gridDim.x - 1) / gridDim.x);
+    const uint64_t v0 = (uint64_t)blockIdx.x * chunk;
+    if (R == 0u || v0 >= all) return;
+    const uint64_t v1 = min(v0 + chunk, all);
+    __shared__ int s_below[2];
+    if (threadIdx.x < 2) s_below[threadIdx.x] = 0;
+    __syncthreads();
+    int n0 = 0, n1 = 0;
+    for (int b = threadIdx.x; b < K; b += T) {
+        const uint64_t at = (uint64_t)p.start[b] + (uint64_t)kBucketCost * (uint64_t)b;
+        n0 += at <= v0 ? 1 : 0;
+        n1 += at <= v1 ? 1 : 0;
+    }
+    if (n0) atomicAdd(&s_below[0], n0);
+    if (n1) atomicAdd(&s_below[1], n1);
+    __syncthreads();
+    auto record = [&](uint64_t v, int b) {
+        const uint64_t first = (uint64_t)p.start[b] + (uint64_t)kBucketCost * (uint64_t)(b + 1);
+        return (uint32_t)(v > first ? min((uint64_t)p.start[b] + (v - first), (uint64_t)p.start[b + 1]) : p.start[b]);
+    };
+    const uint32_t lo = record(v0, s_below[0] - 1), hi = record(v1, s_below[1] - 1);
+    if (lo >= hi) return;
     int chunk_log2 = 0;
-    while ((1u << chunk_log2) < chunk) ++chunk_log2;
-    const uint64_t lo64 = (uint64_t)blockIdx.x * chunk;
-    if (lo64 >= R) return;
-    const uint32_t lo = (uint32_t)lo64;
-    const uint32_t hi = (uint32_t)(lo64 + chunk < R ? lo64 + chunk : R);
+    while ((1u << chunk_log2) < hi - lo) ++chunk_log2;
     const int b0 = (int)(RecT<BIL>::load(p.sorted, lo).key() >> p.shift);
     const int b1 = (int)(RecT<BIL>::load(p.sorted, hi - 1).key() >> p.shift);
     float* accf = (float*)acc;
