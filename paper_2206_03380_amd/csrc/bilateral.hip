@@ -19,10 +19,11 @@
 // FP64 from the FP32 depths (the differences of FP32 values and their products
 // with the small integer offsets are exact there), so the prediction does not
 // lose its digits when the two gradient components cancel along an iso-depth
-// line (scaled by sigma_z ln 2 before the taps: one FP64 product less in each,
-// forward 226 -> 193 us at R = 6, six channels, eight 512 x 512 views).  The
-// three weight factors are combined in one base-2 exponent and a
-// single exp2; colours accumulate in FP32.
+// line.  It is scaled by sigma_z ln 2 only after that sum, by one FP64 FMA that
+// adds eps as well: the scale rounds each component if it is applied to the
+// gradient, and next to eps the two roundings do not cancel.  The three weight
+// factors are combined in one base-2 exponent and a single exp2; colours
+// accumulate in FP32.
 #include <hip/hip_runtime.h>
 #include <math.h>
 
@@ -82,13 +83,13 @@ struct WeightConsts {
 };
 
 // w(p, q) for guides p, q (normal xyz normalised or zero, depth w), the depth
-// gradient at p times sigma_z ln 2 (its y part times dy), and the offset
-// (dx, dy) = q - p, dy2 = dy^2.
+// gradient at p (its y part times dy), and the offset (dx, dy) = q - p,
+// dy2 = dy^2.
 __device__ __forceinline__ float tap_weight(const float4& p, const float4& q, double gx, double gydy, int dx,
                                             float dy2, const WeightConsts& c) {
     const float d = fmaf(p.x, q.x, fmaf(p.y, q.y, p.z * q.z));
     const float lg = __builtin_amdgcn_logf(fmaxf(d, 0.0f));  // log2, -inf at 0
-    const float den = (float)__dadd_rn(fabs(fma(gx, (double)dx, gydy)), c.epsl);
+    const float den = (float)fma(c.szl, fabs(fma(gx, (double)dx, gydy)), c.epsl);
     const float az2 = fabsf(p.w - q.w) * __builtin_amdgcn_rcpf(den);  // |dz| / (pred + eps) * log2(e)
     const float e = fmaf(c.sn, lg, ((float)(dx * dx) + dy2) * c.ks - az2);
     return __builtin_amdgcn_exp2f(e);
@@ -175,8 +176,6 @@ __global__ __launch_bounds__(256) void bilat_fwd_kernel(BilatArgs a, WeightConst
 #pragma unroll
     for (int ch = 0; ch < NC; ++ch) acc[ch] = 0.0f;
     float den = 0.0f;
-    gx *= wc.szl;
-    gy *= wc.szl;
     for (int dy = -R; dy <= R; ++dy) {
         const int row = (py + R + dy) * S + px + R, grow = (py + R + dy) * G + px + R;
         const double gydy = gy * (double)dy;
@@ -198,8 +197,8 @@ __global__ __launch_bounds__(256) void bilat_fwd_kernel(BilatArgs a, WeightConst
 
 // Adjoint: dL/dc(q) = sum_p dL/dout(p) w(p, q) / W(p) over the p whose
 // footprint holds q, i.e. p = q - d for the same offsets d.  The staged
-// region carries each p's guide, its FP64 depth gradient (times sigma_z ln 2)
-// and its upstream gradient already divided by W(p).
+// region carries each p's guide, its FP64 depth gradient and its upstream
+// gradient already divided by W(p).
 template <int R, int NC>
 __global__ __launch_bounds__(256) void bilat_bwd_kernel(BilatArgs a, WeightConsts wc, const float* __restrict__ g_out,
                                                         const float* __restrict__ wsum, float* __restrict__ g_in) {
@@ -221,8 +220,6 @@ __global__ __launch_bounds__(256) void bilat_bwd_kernel(BilatArgs a, WeightConst
             if (a.mask[k]) {
                 g = load_guide(a, k);
                 depth_grad(a.depth, a.mask, t.base, gx, gy, a.W, a.H, d2.x, d2.y);
-                d2.x *= wc.szl;
-                d2.y *= wc.szl;
                 const float W = wsum[k];
                 const float inv = W > 0.0f ? 1.0f / W : 0.0f;
 #pragma unroll
