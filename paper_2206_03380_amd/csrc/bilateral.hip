@@ -38,20 +38,34 @@ constexpr double kLn2 = 0.69314718055994530942;
 
 __host__ __device__ constexpr int lds_stride(int R) { return kT + 2 * R <= 24 ? 24 : 40; }
 
-// Row stride of the guides (gb bytes each) beside nc planes of colours: without
-// padding where one more workgroup then fits in a CU's LDS (160 KB in pieces of
-// 1280 bytes), though two lanes of a tap's guide read then share a bank.  The
-// taps are chains through a logarithm, a reciprocal and an exponential, which
-// other waves hide: six channels, R = 6, eight 512 x 512 views, backward 2 -> 3
-// workgroups, 261 -> 221 us; where the count stays (one channel, R = 3; six,
-// R = 8) no padding costs 12 and 4%.  (Two pixels per lane, which halves the
-// LDS reads, gains 4% backward and loses 3% forward.)
-constexpr int lds_groups(int bytes) { return 163840 / ((bytes + 1279) / 1280 * 1280); }
-__host__ __device__ constexpr int guide_stride(int R, int nc, int gb) {
-    const int rw = kT + 2 * R, S = lds_stride(R), col = rw * S * 4 * nc;
-    const int padded = lds_groups(rw * S * gb + col), packed = lds_groups(rw * rw * gb + col);
-    return (packed > padded && padded < 8) ? rw : S;
+// A kernel has up to two forms, by the number of tiles:
+//  sparse  padded guides and a whole row of taps unrolled, whose LDS reads run
+//          ahead.  The better one while every tile is resident at once, for
+//          most kernels at any size;
+//  dense   where more tiles than that gain from another workgroup per CU:
+//    backward, R = 6, three and six channels: guides without padding, though
+//          two lanes of a tap's guide read then share a bank; 3 -> 4 and 2 -> 3
+//          workgroups of LDS.  Six channels, sparse and dense: 504 tiles 26.9
+//          and 29.9 us, 576 tiles 40.9 and 37.7, 4096 tiles 147 and 129; three
+//          channels 23.0 and 24.9, 33.8 and 31.1, 121 and 107; R = 8, one
+//          channel, 28.8 and 30.6, 54 and 53 at 1024 tiles, 143 and 131.  (The
+//          others lose up to 30% without padding.)
+//    backward, R = 8, six channels: five taps at a time, where a whole row took
+//          256 registers and left one workgroup a CU: 224 tiles 36.8 and 45.9,
+//          400 tiles 56.3 and 46.4, 4096 tiles 338 and 244 us;
+//    forward, R = 7, six channels, the same: 504 tiles 30.0 and 29.9, 576 tiles
+//          43.0 and 38.8, 4096 tiles 152 and 133 us.  (Elsewhere five taps at
+//          a time lose up to 25%.)
+__host__ __device__ constexpr int dense_from(bool bwd, int R, int nc) {   // tiles; 0: no dense form
+    if (bwd) return (R == 6 && nc >= 3) || (R == 8 && nc == 1) ? 512 : (R == 8 && nc == 6 ? 256 : 0);
+    return R == 7 && nc == 6 ? 512 : 0;
 }
+// row stride of the guides
+__host__ __device__ constexpr int guide_stride(bool bwd, int R, int nc, bool dense) {
+    return bwd && dense && (R == 6 || nc == 1) ? kT + 2 * R : lds_stride(R);
+}
+// taps of a row unrolled together
+constexpr int row_unroll(int R, int nc, bool dense) { return dense && R > 6 && nc == 6 ? 5 : 2 * R + 1; }
 
 // Balanced block -> tile bijection: hardware places block b on XCD b % 8;
 // XCD x gets the contiguous tile range starting at x*q + min(x, r).
@@ -118,12 +132,6 @@ __device__ __forceinline__ TileLoc tile_loc(const BilatArgs& a) {
     return TileLoc{(int64_t)v * a.H * a.W, (r % a.tiles_x) * kT, (r / a.tiles_x) * kT};
 }
 
-// Taps of a row unrolled together: all of them up to R = 6, which lets their LDS
-// reads run ahead; 15 and 17 took the adjoint to 256 registers and two waves per
-// SIMD (R = 8, six channels, eight 512 x 512 views: 620 us, five at a time 445;
-// forward 319 -> 299; at R = 6 five at a time lose 2%).
-constexpr int row_unroll(int R) { return R > 6 ? 5 : 2 * R + 1; }
-
 // lane -> pixel inside the tile: wave w covers the 8x8 block (w&1, w>>1)
 __device__ __forceinline__ void lane_pixel(int& px, int& py) {
     const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
@@ -131,10 +139,10 @@ __device__ __forceinline__ void lane_pixel(int& px, int& py) {
     py = (w >> 1) * 8 + (l >> 3);
 }
 
-template <int R, int NC>
+template <int R, int NC, bool DENSE>
 __global__ __launch_bounds__(256) void bilat_fwd_kernel(BilatArgs a, WeightConsts wc, const float* __restrict__ in,
                                                         float* __restrict__ out, float* __restrict__ wsum) {
-    constexpr int S = lds_stride(R), RW = kT + 2 * R, G = guide_stride(R, NC, 16);
+    constexpr int S = lds_stride(R), RW = kT + 2 * R, G = guide_stride(false, R, NC, DENSE);
     __shared__ float4 geo[RW * G];
     __shared__ float col[NC][RW * S];
     const TileLoc t = tile_loc(a);
@@ -180,7 +188,7 @@ __global__ __launch_bounds__(256) void bilat_fwd_kernel(BilatArgs a, WeightConst
         const int row = (py + R + dy) * S + px + R, grow = (py + R + dy) * G + px + R;
         const double gydy = gy * (double)dy;
         const float dy2 = (float)(dy * dy);
-#pragma unroll row_unroll(R)
+#pragma unroll row_unroll(R, NC, DENSE)
         for (int dx = -R; dx <= R; ++dx) {
             const int j = row + dx;
             const float w = tap_weight(gp, geo[grow + dx], gx, gydy, dx, dy2, wc);
@@ -199,10 +207,10 @@ __global__ __launch_bounds__(256) void bilat_fwd_kernel(BilatArgs a, WeightConst
 // footprint holds q, i.e. p = q - d for the same offsets d.  The staged
 // region carries each p's guide, its FP64 depth gradient and its upstream
 // gradient already divided by W(p).
-template <int R, int NC>
+template <int R, int NC, bool DENSE>
 __global__ __launch_bounds__(256) void bilat_bwd_kernel(BilatArgs a, WeightConsts wc, const float* __restrict__ g_out,
                                                         const float* __restrict__ wsum, float* __restrict__ g_in) {
-    constexpr int S = lds_stride(R), RW = kT + 2 * R, G = guide_stride(R, NC, 32);
+    constexpr int S = lds_stride(R), RW = kT + 2 * R, G = guide_stride(true, R, NC, DENSE);
     __shared__ float4 geo[RW * G];
     __shared__ double2 grd[RW * G];
     __shared__ float gw[NC][RW * S];
@@ -246,7 +254,7 @@ __global__ __launch_bounds__(256) void bilat_bwd_kernel(BilatArgs a, WeightConst
             const int row = (py + R - dy) * S + px + R, grow = (py + R - dy) * G + px + R;
             const double ddy = (double)dy;
             const float dy2 = (float)(dy * dy);
-#pragma unroll row_unroll(R)
+#pragma unroll row_unroll(R, NC, DENSE)
             for (int dx = -R; dx <= R; ++dx) {
                 const int j = row - dx;
                 const double2 gp = grd[grow - dx];
@@ -279,14 +287,30 @@ WeightConsts weight_consts(const BilatArgs& a) {
                         kEpsZ * kLn2};
 }
 
+template <int R, int NC, bool BWD, bool DENSE>
+void launch_form(const BilatArgs& a, const WeightConsts& wc, int nb, const float* x, const float* w, float* y,
+                 hipStream_t s) {
+    if constexpr (BWD) bilat_bwd_kernel<R, NC, DENSE><<<nb, 256, 0, s>>>(a, wc, x, w, y);
+    else bilat_fwd_kernel<R, NC, DENSE><<<nb, 256, 0, s>>>(a, wc, x, y, const_cast<float*>(w));
+}
+
+template <int R, int NC, bool BWD>
+void launch(const BilatArgs& a, const WeightConsts& wc, int nb, const float* x, const float* w, float* y,
+            hipStream_t s) {
+    constexpr int from = dense_from(BWD, R, NC);
+    if constexpr (from > 0) {
+        if (nb > from) return launch_form<R, NC, BWD, true>(a, wc, nb, x, w, y, s);
+    }
+    launch_form<R, NC, BWD, false>(a, wc, nb, x, w, y, s);
+}
+
 template <int NC, bool BWD>
 hipError_t dispatch(const BilatArgs& a, const float* x, const float* w, float* y, hipStream_t s) {
     const WeightConsts wc = weight_consts(a);
     const int nb = a.tiles_x * a.tiles_y * a.V;
 #define MCDI_BILAT_CASE(RR)                                                                              \
     case RR:                                                                                             \
-        if (BWD) bilat_bwd_kernel<RR, NC><<<nb, 256, 0, s>>>(a, wc, x, w, y);                           \
-        else bilat_fwd_kernel<RR, NC><<<nb, 256, 0, s>>>(a, wc, x, y, const_cast<float*>(w));          \
+        launch<RR, NC, BWD>(a, wc, nb, x, w, y, s);                                                      \
         break;
     switch (a.R) {
         MCDI_BILAT_CASE(1)
