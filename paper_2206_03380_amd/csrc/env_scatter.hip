@@ -19,15 +19,16 @@
 //      (integer LDS atomics run about six times faster than float ones
 //      here), then one float global add per touched texel channel,
 //      consecutive lanes on consecutive channels (16 per cache line).
-// Fixed point: a chunk adds at most 2^c records of magnitude below 2^e (e from
+// Fixed point: a sum adds at most 2^c records of magnitude below 2^e (e from
 // the bucket's largest |value|, found by the histogram step), so with scale
 // 2^(62-c-e) the int64 sum cannot overflow, and each record is rounded by at
 // most 2^-(63-c-e), i.e. < 2^-(63-c) of the bucket maximum.  The chunks split
 // the records actually written (R, read on the device) and their buckets, each
-// counted as kBucketCost records, over the launch's workgroups; c is the ceiling
-// of the log2 of a chunk's records.  There are min(2048, ceil(capacity / 2^10))
-// workgroups and R <= capacity <= 2^30, so c <= 20 (19 up to 2^30 - 2^22 records): the rounding of one
-// record is below 2^-43 of the bucket maximum.  (Sizing the chunks by the
+// counted as kBucketCost records, over the launch's workgroups.  A sum takes a
+// chunk's records of one bucket, at most 2^c of them with c the ceiling of the
+// log2 of max(2^10, R / g), the records' share of g = min(2048, ceil(capacity /
+// 2^10)) workgroups: R <= capacity <= 2^30, so c <= 19, and the rounding of one
+// record is below 2^-44 of the bucket maximum.  (Sizing the chunks by the
 // capacity instead left most workgroups idle when most samples add nothing:
 // on the 1.0M-triangle room 95% of the shadow rays are blocked, and 8.7M
 // records filled 67 chunks of a 268M-record capacity.)  A bucket with a non-finite value takes
@@ -45,6 +46,7 @@
 // accumulators of the bases whose taps land on it (columns wrapping, rows
 // clamped at the poles).  One record per sample instead of four.
 #include <hip/hip_runtime.h>
+#include <algorithm>
 
 #include "mcdi_internal.h"
 
@@ -55,6 +57,7 @@ constexpr int kMinShift = 10;          // at least 1024 texels per bucket
 constexpr int kMaxShift = 12;          // 4096 texels: 96 KB of LDS per fixed-point bucket copy
 constexpr int kMaxBuckets = 4096;      // 4096 x 4096 texels at most
 constexpr int kGridMax = 2048;
+constexpr int kGridBuckets = 1024;
 constexpr int kBatch = 1024;           // records per LDS sort batch
 constexpr uint32_t kChunkMin = 1024;   // sorted records per accumulate workgroup, at least (with:)
 // Records that clearing and flushing a bucket's sums count as in the split of
@@ -270,9 +273,10 @@ __global__ __launch_bounds__(256) void scatter_kernel(EnvScatter p) {
 }
 
 // acc holds A accumulators of 3 channels per texel of the bucket, [a][texel][3]:
-// A = 1 (nearest) or the four taps (bilinear), flushed into g_env or acc4
+// A = 1 (nearest) or the four taps (bilinear), flushed into g_env or acc4.
+// n_rec_wg: the workgroups that the records alone would have
 template <bool BIL, int T>
-__global__ __launch_bounds__(T) void accumulate_kernel(EnvScatter p) {
+__global__ __launch_bounds__(T) void accumulate_kernel(EnvScatter p, uint32_t n_rec_wg) {
     extern __shared__ long long acc[];   // [A][3 << shift] fixed point (or float in the same space)
     constexpr int A = BIL ? 4 : 1;
     // this workgroup's piece [v0, v1) of the records with kBucketCost entries
@@ -284,91 +288,105 @@ __global__ __launch_bounds__(T) void accumulate_kernel(EnvScatter p) {
     const uint64_t v0 = (uint64_t)blockIdx.x * chunk;
     if (R == 0u || v0 >= all) return;
     const uint64_t v1 = min(v0 + chunk, all);
-    __shared__ int s_below[2];
-    if (threadIdx.x < 2) s_below[threadIdx.x] = 0;
-    __syncthreads();
+    __shared__ int s_below[2][T / 64];
     int n0 = 0, n1 = 0;
     for (int b = threadIdx.x; b < K; b += T) {
         const uint64_t at = (uint64_t)p.start[b] + (uint64_t)kBucketCost * (uint64_t)b;
         n0 += at <= v0 ? 1 : 0;
         n1 += at <= v1 ? 1 : 0;
     }
-    if (n0) atomicAdd(&s_below[0], n0);
-    if (n1) atomicAdd(&s_below[1], n1);
+    for (int o = 32; o > 0; o >>= 1) {
+        n0 += __shfl_xor(n0, o);
+        n1 += __shfl_xor(n1, o);
+    }
+    if ((threadIdx.x & 63) == 0) {
+        s_below[0][threadIdx.x >> 6] = n0;
+        s_below[1][threadIdx.x >> 6] = n1;
+    }
     __syncthreads();
+    n0 = n1 = 0;
+    for (int k = 0; k < T / 64; ++k) {
+        n0 += s_below[0][k];
+        n1 += s_below[1][k];
+    }
+    const int b0 = n0 - 1, b1 = n1 - 1;   // the buckets of the piece's first entry and of the one past its end
     auto record = [&](uint64_t v, int b) {
         const uint64_t first = (uint64_t)p.start[b] + (uint64_t)kBucketCost * (uint64_t)(b + 1);
         return (uint32_t)(v > first ? min((uint64_t)p.start[b] + (v - first), (uint64_t)p.start[b + 1]) : p.start[b]);
     };
-    const uint32_t lo = record(v0, s_below[0] - 1), hi = record(v1, s_below[1] - 1);
+    const uint32_t lo = record(v0, b0), hi = record(v1, b1);
     if (lo >= hi) return;
-    int chunk_log2 = 0;
-    while ((1u << chunk_log2) < hi - lo) ++chunk_log2;
-    const int b0 = (int)(RecT<BIL>::load(p.sorted, lo).key() >> p.shift);
-    const int b1 = (int)(RecT<BIL>::load(p.sorted, hi - 1).key() >> p.shift);
+    // the records of a fixed-point sum at most: 2^c_max, an equal share of the
+    // records alone
+    int c_max = 0;
+    while ((1u << c_max) < max(kChunkMin, (R + n_rec_wg - 1) / n_rec_wg)) ++c_max;
     float* accf = (float*)acc;
     const int slab = 3 << p.shift;       // one accumulator's span in acc
     for (int b = b0; b <= b1; ++b) {
-        const uint32_t s = max(lo, p.start[b]), e = min(hi, p.start[b + 1]);
-        if (s >= e) continue;
-        const int first = b << p.shift;
-        const int n_tex = min(1 << p.shift, p.n_texels - first);
-        const uint32_t mb = p.bmax[b];
-        const bool fixed = mb < 0x7F800000u;   // finite
-        int ex = 0;
-        frexpf(__uint_as_float(mb), &ex);      // every |value| in the bucket < 2^ex
-        const int S = 62 - chunk_log2 - ex;
-        const double scale = ldexp(1.0, S), unscale = ldexp(1.0, -S);
-        for (int a = 0; a < A; ++a)
-            for (int k = threadIdx.x; k < 3 * n_tex; k += T) {
-                if (fixed) acc[a * slab + k] = 0;
-                else accf[2 * (a * slab + k)] = 0.0f;
-            }
-        __syncthreads();
-        for (uint32_t i = s + threadIdx.x; i < e; i += 4 * T) {
-            RecT<BIL> r[4];
+        const uint32_t seg = max(lo, p.start[b]), seg_end = min(hi, p.start[b + 1]);
+        for (uint32_t s = seg; s < seg_end; s += 1u << c_max) {
+            const uint32_t e = min(s + (1u << c_max), seg_end);
+            int chunk_log2 = 0;
+            while ((1u << chunk_log2) < e - s) ++chunk_log2;
+            const int first = b << p.shift;
+            const int n_tex = min(1 << p.shift, p.n_texels - first);
+            const uint32_t mb = p.bmax[b];
+            const bool fixed = mb < 0x7F800000u;   // finite
+            int ex = 0;
+            frexpf(__uint_as_float(mb), &ex);      // every |value| in the bucket < 2^ex
+            const int S = 62 - chunk_log2 - ex;
+            const double scale = ldexp(1.0, S), unscale = ldexp(1.0, -S);
+            for (int a = 0; a < A; ++a)
+                for (int k = threadIdx.x; k < 3 * n_tex; k += T) {
+                    if (fixed) acc[a * slab + k] = 0;
+                    else accf[2 * (a * slab + k)] = 0.0f;
+                }
+            __syncthreads();
+            for (uint32_t i = s + threadIdx.x; i < e; i += 4 * T) {
+                RecT<BIL> r[4];
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
-                if (i + T * j < e) r[j] = RecT<BIL>::load(p.sorted, i + T * j);
+                for (int j = 0; j < 4; ++j)
+                    if (i + T * j < e) r[j] = RecT<BIL>::load(p.sorted, i + T * j);
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                if (i + T * j < e) {
-                    const int k = 3 * (int)(r[j].key() - (uint32_t)first);
-                    float w[A];
-                    if (BIL) {
-                        const float fx = r[j].a.y, fy = r[j].a.z;
-                        w[0] = (1.0f - fx) * (1.0f - fy);
-                        w[A > 1 ? 1 : 0] = fx * (1.0f - fy);
-                        w[A > 2 ? 2 : 0] = (1.0f - fx) * fy;
-                        w[A > 3 ? 3 : 0] = fx * fy;
-                    } else {
-                        w[0] = 1.0f;
-                    }
+                for (int j = 0; j < 4; ++j) {
+                    if (i + T * j < e) {
+                        const int k = 3 * (int)(r[j].key() - (uint32_t)first);
+                        float w[A];
+                        if (BIL) {
+                            const float fx = r[j].a.y, fy = r[j].a.z;
+                            w[0] = (1.0f - fx) * (1.0f - fy);
+                            w[A > 1 ? 1 : 0] = fx * (1.0f - fy);
+                            w[A > 2 ? 2 : 0] = (1.0f - fx) * fy;
+                            w[A > 3 ? 3 : 0] = fx * fy;
+                        } else {
+                            w[0] = 1.0f;
+                        }
 #pragma unroll
-                    for (int a = 0; a < A; ++a) {
+                        for (int a = 0; a < A; ++a) {
 #pragma unroll
-                        for (int c = 0; c < 3; ++c) {
-                            const float v = BIL ? w[a] * r[j].v(c) : r[j].v(c);
-                            if (fixed) {
-                                unsigned long long* ai = (unsigned long long*)acc;
-                                atomicAdd(&ai[a * slab + k + c], (unsigned long long)__double2ll_rn((double)v * scale));
-                            } else {
-                                atomicAdd(&accf[2 * (a * slab + k + c)], v);
+                            for (int c = 0; c < 3; ++c) {
+                                const float v = BIL ? w[a] * r[j].v(c) : r[j].v(c);
+                                if (fixed) {
+                                    unsigned long long* ai = (unsigned long long*)acc;
+                                    atomicAdd(&ai[a * slab + k + c], (unsigned long long)__double2ll_rn((double)v * scale));
+                                } else {
+                                    atomicAdd(&accf[2 * (a * slab + k + c)], v);
+                                }
                             }
                         }
                     }
                 }
             }
-        }
-        __syncthreads();
-        for (int a = 0; a < A; ++a) {
-            float* g = BIL ? p.acc4 + ((size_t)a * p.n_texels + first) * 3 : p.g_env + 3 * (size_t)first;
-            for (int k = threadIdx.x; k < 3 * n_tex; k += T) {
-                const float v = fixed ? (float)((double)acc[a * slab + k] * unscale) : accf[2 * (a * slab + k)];
-                if (v != 0.0f) atomicAdd(g + k, v);
+            __syncthreads();
+            for (int a = 0; a < A; ++a) {
+                float* g = BIL ? p.acc4 + ((size_t)a * p.n_texels + first) * 3 : p.g_env + 3 * (size_t)first;
+                for (int k = threadIdx.x; k < 3 * n_tex; k += T) {
+                    const float v = fixed ? (float)((double)acc[a * slab + k] * unscale) : accf[2 * (a * slab + k)];
+                    if (v != 0.0f) atomicAdd(g + k, v);
+                }
             }
+            __syncthreads();
         }
-        __syncthreads();
     }
 }
 
@@ -394,11 +412,21 @@ __global__ __launch_bounds__(256) void gather_kernel(EnvScatter p) {
     if (v != 0.0f) atomicAdd(p.g_env + k, v);
 }
 
-// workgroups of the accumulation: one per kChunkMin records of capacity, at
-// most kGridMax; each takes an equal share of the records actually written
-unsigned accumulate_grid(uint32_t cap) {
+// workgroups of the accumulation for the records: one per kChunkMin of capacity,
+// at most kGridMax
+unsigned record_grid(uint32_t cap) {
     const uint32_t g = (cap + kChunkMin - 1) / kChunkMin;
     return g < (uint32_t)kGridMax ? g : (unsigned)kGridMax;
+}
+// and with one more for every bucket, up to kGridBuckets: a small image beside a
+// large probe has few records' workgroups and many buckets, and records in one
+// bucket would all be one workgroup's.  The adjoint of a 16 x 16 image at 4 spp
+// on a 1024 x 2048 probe 1002 us by the records' workgroups alone, up to 512,
+// 1024, 2048 and 8192 with the buckets' 68, 65, 64 and 63 us; a 256 x 256 image
+// at 4 spp on a 4096 x 4096 probe 198 us, 190, 195, 209 and 225.
+unsigned accumulate_grid(unsigned n_rec_wg, int K) {
+    const unsigned n = n_rec_wg + (unsigned)K;
+    return std::max(n_rec_wg, std::min(n, (unsigned)kGridBuckets));
 }
 
 }  // namespace
@@ -479,7 +507,8 @@ static hipError_t launch_env_scatter_t(const EnvScatter& p, hipStream_t s) {
         if (e != hipSuccess) return e;
     }
     hipLaunchKernelGGL(scatter_kernel<BIL>, dim3(p.n_wg), dim3(256), lds_sc, s, p);
-    const unsigned grid = accumulate_grid(p.cap);
+    const unsigned n_rec_wg = record_grid(p.cap);
+    const unsigned grid = accumulate_grid(n_rec_wg, p.K);
     const size_t lds_acc = sizeof(long long) * (3u << p.shift) * (BIL ? 4 : 1);
     if (lds_acc > 65536) {   // above the default dynamic LDS limit
         const hipError_t e = hipFuncSetAttribute((const void*)accumulate_kernel<BIL, 1024>,
@@ -491,9 +520,9 @@ static hipError_t launch_env_scatter_t(const EnvScatter& p, hipStream_t s) {
     // workgroups per CU, which then have 1024 threads (6.4M bilinear samples
     // 178 -> 109 us)
     if (lds_acc <= 32768)
-        hipLaunchKernelGGL((accumulate_kernel<BIL, 256>), dim3(grid), dim3(256), lds_acc, s, p);
+        hipLaunchKernelGGL((accumulate_kernel<BIL, 256>), dim3(grid), dim3(256), lds_acc, s, p, n_rec_wg);
     else
-        hipLaunchKernelGGL((accumulate_kernel<BIL, 1024>), dim3(grid), dim3(1024), lds_acc, s, p);
+        hipLaunchKernelGGL((accumulate_kernel<BIL, 1024>), dim3(grid), dim3(1024), lds_acc, s, p, n_rec_wg);
     if (BIL) {
         const int64_t n = 3 * (int64_t)p.H * p.W;
         hipLaunchKernelGGL(gather_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, p);
