@@ -175,99 +175,171 @@ __global__ __launch_bounds__(256) void morton(const float4* tmp, int64_t nt, con
 // bits, and equal centroids, are split by index as equal keys are.
 // 36 walls of a room of 1.0M triangles: 6.1 -> 4.6 node visits a shadow ray
 // (studied on the CPU), shadow rays 7.1 -> 5.4 ms.
+//
+// A thread to each place of three lists, in which a node's triangles are
+// neighbours, by centroid along the list's axis: the boxes on both sides of
+// every plane are a prefix and a suffix box within the node, and a split moves
+// each list's upper side behind its lower one.  Bound by the latency of a level's
+// LDS accesses and barriers (log2 of its largest node's triangles, and four).
+// (Each triangle's thread visiting all triangles for its planes, twice a level,
+// made a build's time with 12, 36, 80 and 128 big triangles beside 600 small ones
+// 104, 160, 261 and 350 us, now 92, 102, 114 and 118; 79 without any.  A wavefront to each axis
+// with two places a lane and shuffles for the scans: 99, 110, 131 and 146.)
 constexpr int kBigSah = 128;
+
+// a box while it is scanned: 16 + 8 bytes
+struct ScanBox {
+    float4 a;   // lo.x, lo.y, lo.z, hi.x
+    float2 b;   // hi.y, hi.z
+    __device__ __forceinline__ void grow(const float4& oa, const float2& ob) {
+        a = make_float4(fminf(a.x, oa.x), fminf(a.y, oa.y), fminf(a.z, oa.z), fmaxf(a.w, oa.w));
+        b = make_float2(fmaxf(b.x, ob.x), fmaxf(b.y, ob.y));
+    }
+    __device__ __forceinline__ float cost(int count) const {
+        const float dx = a.w - a.x, dy = b.x - a.y, dz = b.y - a.z;
+        return (dx * dy + dy * dz + dz * dx) * (float)count;
+    }
+};
+
 __global__ __launch_bounds__(3 * kBigSah) void big_sah(const float4* tmp, int nt, uint64_t* keys, uint32_t* vals,
                                                        const DeviceSceneInfo* info) {
-    __shared__ float lo[3][kBigSah], hi[3][kBigSah], ctr[3][kBigSah];
-    __shared__ unsigned long long code[kBigSah], best[kBigSah];
-    __shared__ int s_more;
+    constexpr int T = 3 * kBigSah;
+    __shared__ float4 s_boxa[kBigSah], s_scana[2][2][T];     // [..][prefix, suffix][..]
+    __shared__ float2 s_boxb[kBigSah], s_scanb[2][2][T];
+    __shared__ float s_ctr[3][kBigSah];           // by triangle, as are s_box, s_code and s_bit
+    __shared__ unsigned long long s_code[kBigSah];
+    __shared__ int s_bit[kBigSah];                // its node's next key bit, -1: not split any more
+    __shared__ int s_list[3][kBigSah];
+    __shared__ int s_begin[kBigSah], s_end[kBigSah];         // the places of the node a place is in
+    __shared__ uint32_t s_cost[kBigSah], s_plane[kBigSah];   // at the node's first place: the least cost, its plane
+    __shared__ unsigned long long s_upper[T / 64];
+    __shared__ int s_largest;
     const int n = info->n_big;
     if (n < 3 || n > kBigSah || n >= nt) return;
-    const int i = threadIdx.x % kBigSah, axis = threadIdx.x / kBigSah;
-    const bool own = axis == 0 && i < n;      // one thread of each triangle
+    const int p = threadIdx.x % kBigSah, axis = threadIdx.x / kBigSah;
+    const bool on = p < n, first = axis == 0 && on;          // one thread of each place
     uint32_t val = 0;
-    if (own) {
-        val = vals[i];
+    if (first) {
+        val = vals[p];
         const float4* t = tmp + 3 * (size_t)val;
-        const float v[3][3] = {{t[0].x, t[1].x, t[2].x}, {t[0].y, t[1].y, t[2].y}, {t[0].z, t[1].z, t[2].z}};
-        for (int a = 0; a < 3; ++a) {
-            lo[a][i] = fminf(v[a][0], fminf(v[a][1], v[a][2]));
-            hi[a][i] = fmaxf(v[a][0], fmaxf(v[a][1], v[a][2]));
-            ctr[a][i] = (v[a][0] + v[a][1] + v[a][2]) * (1.0f / 3.0f);
-        }
-        code[i] = 0ull;
+        const float4 a = t[0], b = t[1], c = t[2];
+        s_boxa[p] = make_float4(fminf(a.x, fminf(b.x, c.x)), fminf(a.y, fminf(b.y, c.y)), fminf(a.z, fminf(b.z, c.z)),
+                                fmaxf(a.x, fmaxf(b.x, c.x)));
+        s_boxb[p] = make_float2(fmaxf(a.y, fmaxf(b.y, c.y)), fmaxf(a.z, fmaxf(b.z, c.z)));
+        s_ctr[0][p] = (a.x + b.x + c.x) * (1.0f / 3.0f);
+        s_ctr[1][p] = (a.y + b.y + c.y) * (1.0f / 3.0f);
+        s_ctr[2][p] = (a.z + b.z + c.z) * (1.0f / 3.0f);
+        s_code[p] = 0ull;
+        s_bit[p] = 62;
+        s_begin[p] = 0;
+        s_end[p] = n;
+        s_cost[p] = s_plane[p] = ~0u;
     }
-    int bit = 62;          // the node's next key bit (the same for all its triangles)
-    bool open = true;      // the node may still be split
     __syncthreads();
-    for (int level = 0; level < 63; ++level) {
-        // the node's first triangle stands for it
-        int rep = i;
-        if (i < n) {
-            const unsigned long long c = code[i];
-            for (int j = i - 1; j >= 0; --j) rep = code[j] == c ? j : rep;
-            if (own) best[i] = ~0ull;
+    if (on) {
+        // (of equal centroids the lowest index comes last, where their plane is)
+        const float c = s_ctr[axis][p];
+        int place = 0;
+        for (int j = 0; j < n; ++j) {
+            const float o = s_ctr[axis][j];
+            place += (o < c || (o == c && j > p)) ? 1 : 0;
         }
-        if (threadIdx.x == 0) s_more = 0;
+        s_list[axis][place] = p;
+    }
+    int largest = n;     // triangles of the level's largest node that may be split
+    __syncthreads();
+    while (largest > 1) {                                    // (every level takes a bit of 63)
+        int t = 0, begin = 0, end = 0, bit = -1, cur = 0;
+        ScanBox pre, suf;    // of the node's triangles up to this place, and from it on
+        if (on) {
+            t = s_list[axis][p];
+            begin = s_begin[p];
+            end = s_end[p];
+            bit = s_bit[t];
+            pre.a = s_boxa[t];
+            pre.b = s_boxb[t];
+            suf = pre;
+            s_scana[0][0][threadIdx.x] = s_scana[0][1][threadIdx.x] = pre.a;
+            s_scanb[0][0][threadIdx.x] = s_scanb[0][1][threadIdx.x] = pre.b;
+        }
+        if (threadIdx.x == 0) s_largest = 0;
         __syncthreads();
-        if (i < n && open) {
-            const unsigned long long c = code[i];
-            const float at = ctr[axis][i];
-            float bl[2][3], bh[2][3];
-            int cnt[2] = {0, 0};
-            for (int s = 0; s < 2; ++s)
-                for (int a = 0; a < 3; ++a) {
-                    bl[s][a] = INFINITY;
-                    bh[s][a] = -INFINITY;
-                }
-            for (int j = 0; j < n; ++j) {
-                if (code[j] != c) continue;
-                const int s = ctr[axis][j] > at ? 1 : 0;
-                for (int q = 0; q < 2; ++q) {
-                    if (q != s) continue;
-                    ++cnt[q];
-                    for (int a = 0; a < 3; ++a) {
-                        bl[q][a] = fminf(bl[q][a], lo[a][j]);
-                        bh[q][a] = fmaxf(bh[q][a], hi[a][j]);
-                    }
-                }
+        for (int o = 1; o < largest; o <<= 1) {
+            if (on) {
+                if (p - o >= begin) pre.grow(s_scana[cur][0][threadIdx.x - o], s_scanb[cur][0][threadIdx.x - o]);
+                if (p + o < end) suf.grow(s_scana[cur][1][threadIdx.x + o], s_scanb[cur][1][threadIdx.x + o]);
+                s_scana[cur ^ 1][0][threadIdx.x] = pre.a;
+                s_scanb[cur ^ 1][0][threadIdx.x] = pre.b;
+                s_scana[cur ^ 1][1][threadIdx.x] = suf.a;
+                s_scanb[cur ^ 1][1][threadIdx.x] = suf.b;
             }
-            if (cnt[1] > 0) {
-                float cost = 0.0f;
-                for (int s = 0; s < 2; ++s) {
-                    const float dx = bh[s][0] - bl[s][0], dy = bh[s][1] - bl[s][1], dz = bh[s][2] - bl[s][2];
-                    cost += (dx * dy + dy * dz + dz * dx) * (float)cnt[s];
-                }
-                if (cost >= 0.0f)
-                    atomicMin(&best[rep], ((unsigned long long)__float_as_uint(cost) << 32) |
-                                              (unsigned long long)(axis << 8 | i));
+            cur ^= 1;
+            __syncthreads();
+        }
+        // the plane at this place's triangle: the least cost of its node, then
+        // of the planes that have it the one of the lowest axis and index
+        uint32_t mine = ~0u;
+        if (bit >= 0 && p + 1 < end && s_ctr[axis][s_list[axis][p + 1]] > s_ctr[axis][t]) {
+            suf.a = s_scana[cur][1][threadIdx.x + 1];
+            suf.b = s_scanb[cur][1][threadIdx.x + 1];
+            float cost = 0.0f;
+            cost += pre.cost(p + 1 - begin);
+            cost += suf.cost(end - p - 1);
+            if (cost >= 0.0f) {
+                mine = __float_as_uint(cost);
+                atomicMin(&s_cost[begin], mine);
             }
         }
         __syncthreads();
-        if (i < n && open) {
-            const unsigned long long b = best[rep];
-            const int a = (int)(b >> 8) & 3, pivot = (int)(b & 255u);
-            int at = bit;
-            if (b != ~0ull)
+        if (mine != ~0u && mine == s_cost[begin]) atomicMin(&s_plane[begin], (uint32_t)(axis << 8 | t));
+        __syncthreads();
+        int at = -1;         // the bit the node's split takes
+        bool upper = false;
+        if (bit >= 0) {
+            const uint32_t b = s_plane[begin];
+            if (b != ~0u) {
+                const int a = (int)(b >> 8), pivot = (int)(b & 255u);
+                at = bit;
                 while (at >= 0 && 2 - at % 3 != a) --at;
-            open = b != ~0ull && at >= 0;
-            if (open) {
-                if (own) {
-                    s_more = 1;
-                    if (ctr[a][i] > ctr[a][pivot]) code[i] |= 1ull << at;
-                }
-                bit = at - 1;
+                upper = at >= 0 && s_ctr[a][t] > s_ctr[a][pivot];
             }
         }
+        const unsigned long long mask = __ballot(upper);
+        if ((threadIdx.x & 63) == 0) s_upper[threadIdx.x >> 6] = mask;
         __syncthreads();
-        if (!s_more) break;       // uniform: written before the barrier, cleared after the next one
+        if (at >= 0) {
+            // upper ones of the list before place q
+            const unsigned long long m0 = s_upper[2 * axis], m1 = s_upper[2 * axis + 1];
+            auto uppers = [&](int q) {
+                return q < 64 ? __popcll(m0 & ((1ull << q) - 1ull))
+                              : __popcll(m0) + (q < 128 ? __popcll(m1 & ((1ull << (q - 64)) - 1ull)) : __popcll(m1));
+            };
+            const int u0 = uppers(begin), u = uppers(p) - u0, middle = end - (uppers(end) - u0);
+            const int place = upper ? middle + u : p - u;
+            s_list[axis][place] = t;
+            if (axis == 0) {
+                s_begin[place] = upper ? middle : begin;
+                s_end[place] = upper ? end : middle;
+                if (upper) s_code[t] |= 1ull << at;
+                s_bit[t] = at - 1;
+                if (p == begin) atomicMax(&s_largest, max(middle - begin, end - middle));
+            }
+        } else if (first) {
+            s_bit[t] = -1;
+        }
+        if (first) s_cost[p] = s_plane[p] = ~0u;
+        __syncthreads();
+        largest = s_largest;      // (uniform: the next write follows a barrier)
         __syncthreads();
     }
-    if (own) {
-        const unsigned long long c = code[i];
-        int rank = 0;
-        for (int j = 0; j < n; ++j) rank += (code[j] < c || (code[j] == c && j < i)) ? 1 : 0;
-        keys[rank] = c;
+    // the nodes stand in the order of their codes; triangles of one keep theirs
+    if (first) s_list[1][s_list[0][p]] = p;                  // a triangle's place
+    __syncthreads();
+    if (first) {
+        const int q = s_list[1][p], begin = s_begin[q], end = s_end[q];
+        int rank = begin;
+        for (int j = begin; j < end; ++j) rank += s_list[0][j] < p ? 1 : 0;
+        keys[rank] = s_code[p];
         vals[rank] = val;
     }
 }
