@@ -22,12 +22,26 @@ def _ptr(t):
     return C.c_void_p(t.data_ptr()) if t is not None else None
 
 
+def _binding(name):
+    """A binding behind torch.cuda's functions, None where this torch has none of
+    that name (the public functions serve then)."""
+    return getattr(torch._C, name, None)
+
+
+_RAW_ALLOC = _binding("_cuda_cudaCachingAllocator_raw_alloc")
+_RAW_DELETE = _binding("_cuda_cudaCachingAllocator_raw_delete")
+_RAW_STREAM = _binding("_cuda_getCurrentRawStream")
+_RAW_DEVICE = _binding("_cuda_getDevice")
+
+
 def _stream(stream=None):
     if stream is not None:
         return C.c_void_p(stream.cuda_stream)
+    if _RAW_STREAM is None or _RAW_DEVICE is None:
+        return C.c_void_p(torch.cuda.current_stream().cuda_stream)
     if not torch.cuda.is_initialized():
         torch.cuda.init()
-    return C.c_void_p(torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()))
+    return C.c_void_p(_RAW_STREAM(_RAW_DEVICE()))
 
 
 def _need(t, dtype, shape=None, name="tensor"):
@@ -54,14 +68,19 @@ def _need(t, dtype, shape=None, name="tensor"):
 @C.CFUNCTYPE(C.c_void_p, C.c_void_p, C.c_size_t, C.c_void_p)
 def _torch_alloc(ctx, nbytes, stream):
     try:
-        return torch._C._cuda_cudaCachingAllocator_raw_alloc(nbytes, stream or 0)
+        if _RAW_ALLOC is None or _RAW_DELETE is None:
+            return torch.cuda.caching_allocator_alloc(nbytes, stream=stream or 0)
+        return _RAW_ALLOC(nbytes, stream or 0)
     except Exception:  # out of memory: report NULL to the library
         return None
 
 
 @C.CFUNCTYPE(None, C.c_void_p, C.c_void_p, C.c_void_p)
 def _torch_free(ctx, ptr, stream):
-    torch._C._cuda_cudaCachingAllocator_raw_delete(ptr)
+    if _RAW_ALLOC is None or _RAW_DELETE is None:
+        torch.cuda.caching_allocator_delete(ptr)
+    else:
+        _RAW_DELETE(ptr)
 
 
 _TORCH_ALLOCATOR = L.Allocator(None, _torch_alloc, _torch_free)
