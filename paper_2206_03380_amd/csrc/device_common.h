@@ -497,6 +497,15 @@ __device__ __forceinline__ int bits_below(uint64_t m) {
     return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
 
+// orders a wavefront's LDS accesses before it against those behind it, of all its
+// lanes among each other (no instruction: the LDS serves a wave in order; the
+// barrier alone only keeps the compiler from moving what has side effects)
+__device__ __forceinline__ void wave_order() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Any-hit query of one ray by a whole wavefront over the 4-wide hierarchy.  The
 // wave keeps one stack of references in LDS: each step takes the top 64 (or
 // all), a lane to each -- a node's hit children go back onto the stack, a
@@ -525,7 +534,7 @@ __device__ __forceinline__ bool wave_anyhit(const Scene& sc, const Ray& r, const
         n -= take;
         bool hit = false;
         uint32_t w[4] = {0u, 0u, 0u, 0u};
-        __builtin_amdgcn_wave_barrier();   // the pushes of the last step come first
+        wave_order();       // the pushes of the last step come first
         if (lane < take) {
             const uint32_t ref = entry(n + lane);
             if (ref & kQLeaf) {
@@ -540,7 +549,7 @@ __device__ __forceinline__ bool wave_anyhit(const Scene& sc, const Ray& r, const
             }
         }
         if (__any(hit)) return true;
-        __builtin_amdgcn_wave_barrier();
+        wave_order();
         uint64_t live[4];
         int total = n;
 #pragma unroll
