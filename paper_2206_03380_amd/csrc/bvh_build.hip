@@ -909,7 +909,9 @@ __global__ __launch_bounds__(256) void wide_groups(const Node* out, const QNode*
 // many levels as a full 4-ary tree needs twice over: what a thinner tree
 // leaves out stays in the node array.
 constexpr int kTopLevels = 6;
-__global__ __launch_bounds__(64) void hoist_top(const QNode* groups, QNode* top) {
+// (A reference that failed the builder's check, never for a valid tree, is read
+// inside the array, whose capacity this is, and no walk takes the wide nodes.)
+__global__ __launch_bounds__(64) void hoist_top(const QNode* groups, uint32_t capacity, QNode* top) {
     static_assert(kTopNodes <= 64, "a lane to each node of a level");
     __shared__ uint32_t s_list[kTopNodes];
     const int t = threadIdx.x;
@@ -940,7 +942,7 @@ __global__ __launch_bounds__(64) void hoist_top(const QNode* groups, QNode* top)
             for (int k = 0; k < 4; ++k) {
                 if (!(g[k].w & kQLeaf)) {
                     if (at < next_end) {
-                        s_list[at] = g[k].w & (kRefTop - 1u);
+                        s_list[at] = min(g[k].w & (kRefTop - 1u), capacity - 1u);
                         g[k].w = (g[k].w & ~(kRefTop - 1u)) | kRefTop | (uint32_t)at;
                     }
                     ++at;
@@ -1149,7 +1151,7 @@ hipError_t build_bvh(const float* verts, int64_t nv, const int32_t* tris, int64_
         if (err == hipSuccess) {
             hipLaunchKernelGGL(wide_groups, dim3(nblk(2 * nt - 1)), dim3(256), 0, s, nodes_out, qnodes_out, gflag,
                                gidx, naxis, 2 * nt - 1, groups_out, info);
-            hipLaunchKernelGGL(hoist_top, dim3(1), dim3(64), 0, s, groups_out, top);
+            hipLaunchKernelGGL(hoist_top, dim3(1), dim3(64), 0, s, groups_out, (uint32_t)nt, top);
             hipLaunchKernelGGL(finish_info, dim3(1), dim3(256), 0, s, nodes_out, eparts, (int)n_part, gflag, gidx,
                                2 * nt - 1, info);
         }
