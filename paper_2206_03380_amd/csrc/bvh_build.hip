@@ -179,12 +179,14 @@ __global__ __launch_bounds__(256) void morton(const float4* tmp, int64_t nt, con
 // A thread to each place of three lists, in which a node's triangles are
 // neighbours, by centroid along the list's axis: the boxes on both sides of
 // every plane are a prefix and a suffix box within the node, and a split moves
-// each list's upper side behind its lower one.  Bound by the latency of a level's
-// LDS accesses and barriers (log2 of its largest node's triangles, and four).
+// each list's upper side behind its lower one.  The scans run in rows of 16
+// lanes by data-parallel moves and take the other rows' ends from LDS.  Bound by
+// the latency of a level's LDS accesses and its five barriers.
 // (Each triangle's thread visiting all triangles for its planes, twice a level,
 // made a build's time with 12, 36, 80 and 128 big triangles beside 600 small ones
-// 104, 160, 261 and 350 us, now 92, 102, 114 and 118; 79 without any.  A wavefront to each axis
-// with two places a lane and shuffles for the scans: 99, 110, 131 and 146.)
+// 104, 160, 261 and 350 us, now 91, 99, 110 and 114; 79 without any.  Scans by shuffles, two
+// places a lane: 99, 110, 131 and 146; in LDS with a barrier a step: 92, 102, 114
+// and 118.)
 constexpr int kBigSah = 128;
 
 // a box while it is scanned: 16 + 8 bytes
@@ -195,17 +197,38 @@ struct ScanBox {
         a = make_float4(fminf(a.x, oa.x), fminf(a.y, oa.y), fminf(a.z, oa.z), fmaxf(a.w, oa.w));
         b = make_float2(fmaxf(b.x, ob.x), fmaxf(b.y, ob.y));
     }
-    __device__ __forceinline__ float cost(int count) const {
+    __device__ __forceinline__ float area() const {   // half of it
         const float dx = a.w - a.x, dy = b.x - a.y, dz = b.y - a.z;
-        return (dx * dy + dy * dz + dz * dx) * (float)count;
+        return fmaf(dz, dx, fmaf(dx, dy, dy * dz));
     }
 };
+
+// the value of the lane O before (row_shr) or behind (row_shl) in its row of 16
+// lanes; undefined where the row has none
+template <int CTRL>
+__device__ __forceinline__ float row_move(float x) {
+    const int v = __builtin_bit_cast(int, x);
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(v, v, CTRL, 0xF, 0xF, false));
+}
+template <int CTRL>
+__device__ __forceinline__ ScanBox row_move(const ScanBox& s) {
+    return ScanBox{make_float4(row_move<CTRL>(s.a.x), row_move<CTRL>(s.a.y), row_move<CTRL>(s.a.z), row_move<CTRL>(s.a.w)),
+                   make_float2(row_move<CTRL>(s.b.x), row_move<CTRL>(s.b.y))};
+}
+// one step of the scans within a row: of places [begin, p], and of (p, end)
+template <int O>
+__device__ __forceinline__ void row_scan(int p, int begin, int end, ScanBox& pre, ScanBox& suf) {
+    const ScanBox before = row_move<0x110 + O>(pre), behind = row_move<0x100 + O>(suf);
+    if ((p & 15) >= O && p - O >= begin) pre.grow(before.a, before.b);
+    if ((p & 15) + O < 16 && p + O < end) suf.grow(behind.a, behind.b);
+}
 
 __global__ __launch_bounds__(3 * kBigSah) void big_sah(const float4* tmp, int nt, uint64_t* keys, uint32_t* vals,
                                                        const DeviceSceneInfo* info) {
     constexpr int T = 3 * kBigSah;
-    __shared__ float4 s_boxa[kBigSah], s_scana[2][2][T];     // [..][prefix, suffix][..]
-    __shared__ float2 s_boxb[kBigSah], s_scanb[2][2][T];
+    __shared__ float4 s_boxa[kBigSah];
+    __shared__ float2 s_boxb[kBigSah];
+    __shared__ ScanBox s_pre[T / 16], s_suf[T / 16];         // by row: its last place's prefix, its first one's suffix
     __shared__ float s_ctr[3][kBigSah];           // by triangle, as are s_box, s_code and s_bit
     __shared__ unsigned long long s_code[kBigSah];
     __shared__ int s_bit[kBigSah];                // its node's next key bit, -1: not split any more
@@ -213,7 +236,7 @@ __global__ __launch_bounds__(3 * kBigSah) void big_sah(const float4* tmp, int nt
     __shared__ int s_begin[kBigSah], s_end[kBigSah];         // the places of the node a place is in
     __shared__ uint32_t s_cost[kBigSah], s_plane[kBigSah];   // at the node's first place: the least cost, its plane
     __shared__ unsigned long long s_upper[T / 64];
-    __shared__ int s_largest;
+    __shared__ int s_largest[2];                  // by the level's parity
     const int n = info->n_big;
     if (n < 3 || n > kBigSah || n >= nt) return;
     const int p = threadIdx.x % kBigSah, axis = threadIdx.x / kBigSah;
@@ -248,9 +271,10 @@ __global__ __launch_bounds__(3 * kBigSah) void big_sah(const float4* tmp, int nt
     }
     int largest = n;     // triangles of the level's largest node that may be split
     __syncthreads();
-    while (largest > 1) {                                    // (every level takes a bit of 63)
-        int t = 0, begin = 0, end = 0, bit = -1, cur = 0;
-        ScanBox pre, suf;    // of the node's triangles up to this place, and from it on
+    for (int level = 0; largest > 1; ++level) {              // (every level takes a bit of 63)
+        int t = 0, begin = 0, end = 0, bit = -1;
+        ScanBox pre{}, suf{};    // of the node's triangles up to this place, and behind it
+        float next = 0.0f;       // the centroid behind it
         if (on) {
             t = s_list[axis][p];
             begin = s_begin[p];
@@ -258,33 +282,36 @@ __global__ __launch_bounds__(3 * kBigSah) void big_sah(const float4* tmp, int nt
             bit = s_bit[t];
             pre.a = s_boxa[t];
             pre.b = s_boxb[t];
-            suf = pre;
-            s_scana[0][0][threadIdx.x] = s_scana[0][1][threadIdx.x] = pre.a;
-            s_scanb[0][0][threadIdx.x] = s_scanb[0][1][threadIdx.x] = pre.b;
-        }
-        if (threadIdx.x == 0) s_largest = 0;
-        __syncthreads();
-        for (int o = 1; o < largest; o <<= 1) {
-            if (on) {
-                if (p - o >= begin) pre.grow(s_scana[cur][0][threadIdx.x - o], s_scanb[cur][0][threadIdx.x - o]);
-                if (p + o < end) suf.grow(s_scana[cur][1][threadIdx.x + o], s_scanb[cur][1][threadIdx.x + o]);
-                s_scana[cur ^ 1][0][threadIdx.x] = pre.a;
-                s_scanb[cur ^ 1][0][threadIdx.x] = pre.b;
-                s_scana[cur ^ 1][1][threadIdx.x] = suf.a;
-                s_scanb[cur ^ 1][1][threadIdx.x] = suf.b;
+            suf.a = make_float4(INFINITY, INFINITY, INFINITY, -INFINITY);
+            suf.b = make_float2(-INFINITY, -INFINITY);
+            if (p + 1 < end) {
+                const int t1 = s_list[axis][p + 1];
+                suf.a = s_boxa[t1];
+                suf.b = s_boxb[t1];
+                next = s_ctr[axis][t1];
             }
-            cur ^= 1;
-            __syncthreads();
+        }
+        if (threadIdx.x == 0) s_largest[level & 1] = 0;
+        row_scan<1>(p, begin, end, pre, suf);
+        if (largest > 2) row_scan<2>(p, begin, end, pre, suf);
+        if (largest > 4) row_scan<4>(p, begin, end, pre, suf);
+        if (largest > 8) row_scan<8>(p, begin, end, pre, suf);
+        const int row = threadIdx.x >> 4;
+        if ((p & 15) == 15) s_pre[row] = pre;
+        if ((p & 15) == 0) s_suf[row] = suf;
+        __syncthreads();
+        if (bit >= 0) {
+            const int row0 = row - (p >> 4);     // the list's first
+            for (int r = row0 + (begin >> 4); r < row; ++r) pre.grow(s_pre[r].a, s_pre[r].b);
+            for (int r = row + 1; 16 * (r - row0) < end - 1; ++r) suf.grow(s_suf[r].a, s_suf[r].b);
         }
         // the plane at this place's triangle: the least cost of its node, then
         // of the planes that have it the one of the lowest axis and index
         uint32_t mine = ~0u;
-        if (bit >= 0 && p + 1 < end && s_ctr[axis][s_list[axis][p + 1]] > s_ctr[axis][t]) {
-            suf.a = s_scana[cur][1][threadIdx.x + 1];
-            suf.b = s_scanb[cur][1][threadIdx.x + 1];
-            float cost = 0.0f;
-            cost += pre.cost(p + 1 - begin);
-            cost += suf.cost(end - p - 1);
+        if (bit >= 0 && p + 1 < end && next > s_ctr[axis][t]) {
+            // (written out: the same two sets along several axes are told apart
+            // by its rounding, which the compiler's choice of fusions would change)
+            const float cost = fmaf(suf.area(), (float)(end - p - 1), pre.area() * (float)(p + 1 - begin));
             if (cost >= 0.0f) {
                 mine = __float_as_uint(cost);
                 atomicMin(&s_cost[begin], mine);
@@ -322,15 +349,14 @@ __global__ __launch_bounds__(3 * kBigSah) void big_sah(const float4* tmp, int nt
                 s_end[place] = upper ? end : middle;
                 if (upper) s_code[t] |= 1ull << at;
                 s_bit[t] = at - 1;
-                if (p == begin) atomicMax(&s_largest, max(middle - begin, end - middle));
+                if (p == begin) atomicMax(&s_largest[level & 1], max(middle - begin, end - middle));
             }
         } else if (first) {
             s_bit[t] = -1;
         }
         if (first) s_cost[p] = s_plane[p] = ~0u;
         __syncthreads();
-        largest = s_largest;      // (uniform: the next write follows a barrier)
-        __syncthreads();
+        largest = s_largest[level & 1];      // (uniform: the next level writes the other one)
     }
     // the nodes stand in the order of their codes; triangles of one keep theirs
     if (first) s_list[1][s_list[0][p]] = p;                  // a triangle's place
