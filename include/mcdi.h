@@ -113,7 +113,8 @@ typedef struct {
     int32_t max_depth;    /* longest root-to-leaf path */
     int32_t bad_tris;     /* triangles replaced by degenerate ones */
     int32_t n_groups;     /* 4-wide nodes */
-    int32_t wide;         /* 1: volume-filling geometry (depth complexity of at least 4), 0: surfaces */
+    int32_t wide;         /* 1: volume-filling geometry (depth complexity of at least 4), 0: surfaces; of the
+                           * walks, only the edge gradient's of many rays takes it into account */
     float depth_complexity; /* sum of the leaf boxes' surface areas over the root box's */
     int32_t n_big;        /* big triangles (see mcdi_build_scene) */
 } mcdi_scene_info_t;
@@ -127,7 +128,7 @@ mcdi_status mcdi_scene_info(mcdi_scene scene, mcdi_scene_info_t* info);
  *          float lo[3], int32 escape, float hi[3], int32 payload.  escape is
  *          the index just past the node's subtree (node 0: the node count);
  *          payload 0 = internal node (first child at index + 1), else
- *          (first_triangle << 3) | count (1..4) of a leaf;
+ *          (first_triangle << 3) | count (1 or 2) of a leaf;
  *   tris   n_tris x 12 floats: the triangles in leaf order, three vertices
  *          of (x, y, z, 0).
  * Byte counts: 32 n_nodes and 48 n_tris. */

@@ -446,13 +446,15 @@ __device__ __forceinline__ void gen_tile(const ShadeArgs& A, int64_t tile, float
 //    triangle of a leaf with more advances its reference by 3: the first
 //    index grows by one and the rest drops by one.
 //
-//    What bounds it: instruction issue (99% of the vector issue slots on a
-//    room of 1.0M triangles) and, where the nodes come from the L1 cache, its
+//    What bounds it: instruction issue (93% of the vector issue slots at four
+//    cycles an instruction, in a room of 1.0M triangles and on a 101k-triangle
+//    surface) and, where the nodes come from the L1 cache, its
 //    gathers: 64 lanes at 64 addresses take it about 45 cycles whether a lane
 //    fetches 4 bytes or 16 and whether the four loads of a node share a line
 //    (measured), so a wide node costs 180 of them beside 110 cycles of its
 //    CU's vector issue.  The root's first kTopNodes descendants are therefore
-//    read from LDS (81% of the visits in the room, 30% on a surface), the
+//    read from LDS (L1 accesses per box test, the triangles' included, 1.16 ->
+//    0.59 in the room, 1.13 -> 0.96 on the surface), the
 //    visit order comes with the records instead of by a fifth load, and the
 //    loop holds one walk: a ray whose stack overflows, and it alone, walks the
 //    binary nodes after the visits of the step.
